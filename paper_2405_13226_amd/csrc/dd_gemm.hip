@@ -9,28 +9,47 @@
 // gradient dx = dy W^T is (dy, W^T) and its weight gradient dW = x^T dy is
 // (x^T, dy).
 //
-// One workgroup (8 waves) computes a 256 x 256 tile of C; wave (wm, wn) owns
-// rows 128 wm .. +127 and columns 64 wn .. +63, i.e. 4 x 2 blocks of the
-// 32x32x16 bf16 product.  The K axis is walked in 64-wide steps: the A and B
-// tiles of a step are four 64 x 64 sub-tiles each, in two LDS stages, one
-// barrier per step.  Every sub-tile sits in LDS as the matrix stores it, in
-// the attention kernels' swizzled row-major layout.  An operand stored with
-// its reduction axis along the rows (A^T, B) is read with the transposing
-// LDS read; one stored with it along the columns is read row-wise.  Both
-// give a lane the 8 consecutive k of its row or column.  When both operands
-// are read row-wise (A, B^T: the input gradients), the next step's
-// sub-tiles arrive by direct global->LDS loads of whole 128-byte rows during
-// the current step's products.  Otherwise they are
-// loaded into registers (16 bytes per lane and sub-tile) during the products
-// and written to the other stage after them: after a direct load the
-// compiler waits for it before every transposing LDS read.
+// One workgroup (8 waves) computes a 256 x 256 tile of C.  The K axis is
+// walked in 64-wide steps; the A and B tiles of a step are two halves of 128
+// rows (columns) each, in two LDS stages (128 KiB).  Wave (wm, wn) owns rows
+// 64 wm .. +63 of each A half and columns 32 wn .. +31 of each B half: four
+// 64 x 32 quadrants, one per pair of halves.  A step is four phases, one
+// quadrant's 16 products each:
+//
+//   phase            1        2        3        4
+//   products         A0 B0    A0 B1    A1 B1    A1 B0
+//   LDS reads        B0       B1       A1       A0 of the next step
+//   loads started    A0       B0       B1       A1, all of step + 2
+//
+// The loads refill the half that the phase before has read, so each has six
+// phases (1.5 steps) to arrive; a phase waits only for the loads that the
+// next phase's reads need (vmcnt(12): six halves stay in flight).  Waves 4-7
+// run half a phase behind waves 0-3 (one extra barrier before the loop): on
+// every SIMD one wave issues its 16 products while the other reads its next
+// operands and starts loads.  Loads go directly from global memory to LDS
+// and waits are explicit: the compiler would otherwise wait for every load
+// before each transposing LDS read.
+//
+// What bounds it: power.  At 8192^3 the matrix pipes are busy 87% of the
+// time (0.50 with one barrier per step and all waves in phase) at a shader
+// clock of 1.5-1.6 GHz; the 32x32x16 product keeps them 89% busy at 1.35 GHz
+// and is 7% slower, so the 16x16x32 product is used.  Measured (TFLOP/s,
+// before -> now): 8192^3 A B^T 1,134 -> 1,480, A B 1,068 -> 1,373, A^T B 997
+// -> 1,420; 65,536 x 5632 x 2048 A B^T 1,151 -> 1,420; 2048 x 5632 x 65,536
+// A^T B 863 -> 1,173.
+//
+// Every 64 x 64 sub-tile sits in LDS as the matrix stores it, 128-byte rows
+// of swizzled 16-byte chunks.  An operand stored with its reduction axis
+// along the rows (A^T, B) is read with the transposing LDS read; one stored
+// with it along the columns is read row-wise.  Both give a lane the 8
+// consecutive k of its row or column.
 //
 // Each product is issued as D = op(B)^T op(A)^T, so a lane's accumulator holds
-// 4 consecutive columns of C in each register group: the epilogue writes 8
-// bytes per lane and register group to an LDS copy of the tile, and the tile
-// then goes to memory in full 16-byte rows.  With split-K (weight gradients,
-// whose reduction axis is the 65,536 tokens), every split writes an fp32
-// partial tile to the caller's workspace and a second kernel sums them.
+// 4 consecutive columns of C: the epilogue writes 8 bytes per lane and
+// accumulator to an LDS copy of the tile, and the tile then goes to memory
+// in full 16-byte rows.  With split-K (weight gradients, whose reduction axis
+// is the 65,536 tokens), every split writes an fp32 partial tile to the
+// caller's workspace and a second kernel sums them.
 #include "dd_device.hpp"
 #include "dd_tile.hpp"
 #include "dd_internal.h"
@@ -44,25 +63,60 @@ namespace dd {
 struct GemmTile {
     static constexpr int BM = 256, BN = 256, BK = 64, NW = 8;
     static constexpr int SUB = 64 * 64;        // elements of one 64 x 64 sub-tile
-    static constexpr int HALF = 4 * SUB;       // the A (or B) tile of one K step
+    static constexpr int HALF = 2 * SUB;       // half of the A (or B) tile of one K step
+    static constexpr int SIDE = 4 * HALF;      // A (or B): two halves x two stages
 };
 
+// Waits until at most N of this wave's vector-memory operations are in
+// flight and all its LDS reads have returned, then joins the workgroup's
+// barrier.
+template <int N>
+__device__ __forceinline__ void wait_and_barrier()
+{
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(N) : "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+__device__ __forceinline__ void plain_barrier()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_barrier" : : : "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// Chunk swizzle of the sub-tiles that are read along rows: 64 lanes read 16
+// consecutive rows at four neighbouring chunks, and the LDS serves them in
+// groups of 16 lanes that are not consecutive (lanes 0-3, 12-15, 20-23,
+// 24-27 and so on).  With swz<64>, made for 32 rows at two chunks, such a
+// read has two-way bank conflicts.
+__device__ __forceinline__ int row_swz(int r) { return (r >> 1) & 7; }
+
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+// Row strides (elements) from which a load's per-lane byte offset, up to 7
+// rows, may not fit 32 bits; the loads then take per-lane 64-bit addresses.
+constexpr long long kGemmWideStride = 1LL << 28;
+
 // TA: A is stored [K][M]; TB: B is stored [N][K]; PART: write an fp32
-// partial tile of split blockIdx.y to P ([splits][M][N]) instead of C.
+// partial tile of split blockIdx.y to P ([splits][M][N]) instead of C; WIDE:
+// a row stride of A or B is at least kGemmWideStride.
 // R (optional, not with PART): a bf16 matrix with row stride ldc added to
 // the rounded product before the final rounding (C may be R itself).
-template <bool TA, bool TB, bool PART>
+template <bool TA, bool TB, bool PART, bool WIDE>
 __global__ void __launch_bounds__(512, 1)
 gemm_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint16_t *C,
             float *__restrict__ P, const uint16_t *R, int M, int N, int K, long long lda,
             long long ldb, long long ldc, int k_len)
 {
     using T = GemmTile;
-    // Two K-step stages (A then B sub-tiles each), reused by the epilogue.
-    __shared__ __attribute__((aligned(1024))) uint16_t lds[4 * T::HALF];
+    __shared__ __attribute__((aligned(1024))) uint16_t lds[2 * T::SIDE];
 
     const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int l16 = lane & 15, g = lane >> 4;
     const int wm = wave >> 2, wn = wave & 3;
     const int tiles_n = N / T::BN;
     // Workgroups are dispatched round-robin over the 8 XCDs (block id % 8),
@@ -89,220 +143,226 @@ gemm_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint
     const int kbeg = static_cast<int>(blockIdx.y) * k_len;
     const int nkt = min(k_len, K - kbeg) / T::BK;
 
-    // A 64 x 64 sub-tile (8 KiB) is stored as the matrix stores it, rows of
-    // 128 bytes in the tile_off<64> layout: an operand whose reduction axis
-    // runs along the rows (A^T, B) is read with the transposing LDS read, one
-    // whose reduction axis runs along the columns (A, B^T) row-wise.  (A
-    // layout of 16-column slabs for the row-wise operands, conflict-free on
-    // paper, measured 0.86 LDS bank-conflict cycles per LDS instruction.)
-    // Every lane loads 16 bytes of each sub-tile per K step: row q / 8,
-    // chunk q % 8 (q = 64 wave + lane), so a load instruction reads eight
-    // whole 128-byte row pieces.  The host guarantees that every tile lies
-    // inside the matrices (M, N multiples of 256, K of 64): no load needs
-    // clamping.
-    const int q = wave * 64 + lane, qr = q >> 3, qc = q & 7;
-    const uint16_t *pa = A + qr * lda + qc * 8 +
+    // Loads: sub-tile rows of 128 bytes, eight of them per wave instruction
+    // (1 KiB); lane i takes row 8 wave + i / 8, stored chunk i % 8.
+    const int qr = lane >> 3, qrow = 8 * wave + qr;
+    const int xa = ((lane & 7) ^ (TA ? swz<64>(qrow) : row_swz(qrow))) * 8;
+    const int xb = ((lane & 7) ^ (TB ? row_swz(qrow) : swz<64>(qrow))) * 8;
+    const long long va = (qr * lda + xa) * 2, vb = (qr * ldb + xb) * 2;  // bytes
+    const uint16_t *pa = A + 8 * wave * lda +
                          (TA ? static_cast<long long>(kbeg) * lda + m0 : static_cast<long long>(m0) * lda + kbeg);
-    const uint16_t *pb = B + qr * ldb + qc * 8 +
+    const uint16_t *pb = B + 8 * wave * ldb +
                          (TB ? static_cast<long long>(n0) * ldb + kbeg : static_cast<long long>(kbeg) * ldb + n0);
-    // LDS position of this lane's chunk.
-    const int wpos = qr * 64 + 8 * (qc ^ swz<64>(qr));
     // Sub-tile s starts 64 rows (stored along the tile's rows) or 64 columns
     // further; K step kt moves 64 rows or columns.
     const long long sa = TA ? 64 : 64 * lda, sb = TB ? 64 * ldb : 64;
     const long long ka = TA ? 64 * lda : 64, kb = TB ? 64 : 64 * ldb;
-    u32x4 ra[4], rb[4];
-    auto load = [&](int kt) __attribute__((always_inline)) {
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            ra[s] = *reinterpret_cast<const u32x4 *>(pa + kt * ka + s * sa);
-            rb[s] = *reinterpret_cast<const u32x4 *>(pb + kt * kb + s * sb);
-        }
+    const uint32_t lds0 = lds_base_sgpr(lds) + 1024u * wave;
+    auto load = [&](const uint16_t *p, long long v, uint32_t l) __attribute__((always_inline)) {
+        if constexpr (WIDE)
+            dma_b128(reinterpret_cast<const char *>(p) + v, l);
+        else
+            dma_b128_off(p, static_cast<uint32_t>(v), l);
     };
-    auto store = [&](uint16_t *stage) __attribute__((always_inline)) {
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            *reinterpret_cast<u32x4 *>(stage + s * T::SUB + wpos) = ra[s];
-            *reinterpret_cast<u32x4 *>(stage + T::HALF + s * T::SUB + wpos) = rb[s];
-        }
+    // Half h of A (B) of the K step that pa (pb) points at, into stage S.
+    auto load_a = [&](int h, int S, const uint16_t *p) __attribute__((always_inline)) {
+        const uint32_t l = lds0 + 2u * (2 * h + S) * T::HALF;
+        load(p + 2 * h * sa, va, l);
+        load(p + 2 * h * sa + sa, va, l + 2u * T::SUB);
+    };
+    auto load_b = [&](int h, int S, const uint16_t *p) __attribute__((always_inline)) {
+        const uint32_t l = lds0 + 2u * (T::SIDE + (2 * h + S) * T::HALF);
+        load(p + 2 * h * sb, vb, l);
+        load(p + 2 * h * sb + sb, vb, l + 2u * T::SUB);
     };
 
-    // Transposed reads (elements within a sub-tile, sub-step 0): rows
-    // 8 g + e (and + 4), columns co + 16 (G & 1) + 4 c, for column offsets
-    // co = 0 and 32.
-    const int G16 = lane >> 4, e4 = (lane & 15) >> 2, c4 = lane & 3;
-    auto tr_off = [&](int co, int hh) __attribute__((always_inline)) {
-        return tile_off<64>(8 * g + 4 * hh + e4, co + 16 * (G16 & 1) + 4 * c4);
-    };
-    // Fragment i of A: rows (m) 32 i .. +31 of the wave's 128, sub-tile
-    // 2 wm + i / 2; fragment j of B: columns 32 j .. +31 of the wave's 64,
-    // sub-tile wn.  Transposed reads of sub-step kk: + 16 rows.  Row reads:
-    // rows at tile_off<64>(row, 16 kk + 8 g); the swizzle depends on the row
-    // mod 16, so rows 32 further are 32 * 64 elements further.
-    constexpr bool kDirect = !TA && TB;
-    int dro[4];
+    // Fragments.  A half h: rows 64 wm + 16 i .. +15 of the half, i.e.
+    // sub-tile wm; B half h: columns 32 wn + 16 j .. +15, i.e. sub-tile
+    // wn / 2.  A lane holds the eight k = 32 kk + 8 g .. +7 of its row.
+    // Row reads take them in one piece; transposed reads in two pieces of
+    // four k, whose lane 4 e + c of a 16-lane group addresses row e, columns
+    // 4 c .. 4 c + 3.
+    const int e4 = l16 >> 2, c4 = l16 & 3;
+    const uint16_t *fa[TA ? 8 : 2], *fb[TB ? 2 : 4];
+    {
+        const uint16_t *as = lds + wm * T::SUB;
+        const uint16_t *bs = lds + T::SIDE + (wn >> 1) * T::SUB;
+        if constexpr (TA) {
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
-        dro[kk] = tile_off<64>(l32, 16 * kk + 8 * g);
-    auto a_frag = [&](const uint16_t *at, int i, int kk) __attribute__((always_inline)) {
-        const uint16_t *sub = at + (2 * wm + (i >> 1)) * T::SUB;
-        const int mo = 32 * (i & 1);
-        if constexpr (!TA)
-            return lds_row8(sub + mo * 64 + dro[kk]);
-        else
-            return join(lds_tr4(sub + kk * 1024 + tr_off(mo, 0)),
-                        lds_tr4(sub + kk * 1024 + tr_off(mo, 1)));
-    };
-    auto b_frag = [&](const uint16_t *bt, int j, int kk) __attribute__((always_inline)) {
-        const uint16_t *sub = bt + wn * T::SUB;
-        const int no = 32 * j;
-        if constexpr (TB)
-            return lds_row8(sub + no * 64 + dro[kk]);
-        else
-            return join(lds_tr4(sub + kk * 1024 + tr_off(no, 0)),
-                        lds_tr4(sub + kk * 1024 + tr_off(no, 1)));
-    };
-
-    f32x16 acc[4][2];
+            for (int i = 0; i < 8; ++i)
+                fa[i] = as + tile_off<64>(8 * g + 4 * (i & 1) + e4, 16 * (i >> 1) + 4 * c4);
+        } else {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+            for (int kk = 0; kk < 2; ++kk)
+                fa[kk] = as + 64 * l16 + (((4 * kk + g) ^ row_swz(l16)) << 3);
+        }
+        if constexpr (TB) {
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk)
+                fb[kk] = bs + 64 * (32 * (wn & 1) + l16) + (((4 * kk + g) ^ row_swz(l16)) << 3);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                fb[j] = bs + tile_off<64>(8 * g + 4 * (j & 1) + e4,
+                                          32 * (wn & 1) + 16 * (j >> 1) + 4 * c4);
+        }
+    }
+    bf16x8 a0[4][2], a1[4][2], b0[2][2], b1[2][2];
+    auto read_a = [&](bf16x8 (&f)[4][2], int h, int S) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) {
+                const int o = (2 * h + S) * T::HALF;
+                if constexpr (TA)
+                    f[i][kk] = join(lds_tr4(fa[2 * i] + (o + 2048 * kk)),
+                                    lds_tr4(fa[2 * i + 1] + (o + 2048 * kk)));
+                else
+                    f[i][kk] = lds_row8(fa[kk] + (o + 1024 * i));
+            }
+    };
+    auto read_b = [&](bf16x8 (&f)[2][2], int h, int S) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-            acc[i][j] = f32x16{};
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) {
+                const int o = (2 * h + S) * T::HALF;
+                if constexpr (TB)
+                    f[j][kk] = lds_row8(fb[kk] + (o + 1024 * j));
+                else
+                    f[j][kk] = join(lds_tr4(fb[2 * j] + (o + 2048 * kk)),
+                                    lds_tr4(fb[2 * j + 1] + (o + 2048 * kk)));
+            }
+    };
 
-    // The 32 products of a K step, with the LDS reads issued kAhead reads
-    // ahead of the matrix pipe (then the rest spread over the products) so
-    // that their latency overlaps earlier products (measured 3-6% faster
-    // than the compiler's order).
-    auto compute = [&](const uint16_t *stage) __attribute__((always_inline)) {
-        const uint16_t *at = stage, *bt = stage + T::HALF;
-        __builtin_amdgcn_sched_barrier(0);
+    f32x4 acc[2][2][4][2];  // [A half][B half][i][j]
 #pragma unroll
-        for (int kk = 0; kk < T::BK / 16; ++kk) {
-            bf16x8 af[4], bf[2];
+    for (int x = 0; x < 4; ++x)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                af[i] = a_frag(at, i, kk);
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int j = 0; j < 2; ++j)
-                bf[j] = b_frag(bt, j, kk);
+                acc[x >> 1][x & 1][i][j] = f32x4{};
+    auto products = [&](f32x4 (&c)[4][2], const bf16x8 (&a)[4][2],
+                        const bf16x8 (&b)[2][2]) __attribute__((always_inline)) {
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
-                    acc[i][j] = mfma32(bf[j], af[i], acc[i][j]);  // rows n, columns m
-        }
-        // reads per K step: A 16 row reads or 32 transposed halves, B 8 row
-        // reads or 16 transposed halves
-        constexpr int kAhead = 8;
-        constexpr int NR = (TA ? 32 : 16) + (TB ? 8 : 16);
-        constexpr int NP = 32;
-        constexpr int QR = (NR - kAhead) / NP, RR = (NR - kAhead) % NP;
-        __builtin_amdgcn_sched_group_barrier(0x100, kAhead, 0);
-#pragma unroll
-        for (int i = 0; i < RR; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, QR + 1, 0);
-        }
-#pragma unroll
-        for (int i = RR; i < NP; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if constexpr (QR > 0)
-                __builtin_amdgcn_sched_group_barrier(0x100, QR, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
+                    c[i][j] = mfma16(b[j][kk], a[i][kk], c[i][j]);  // rows n, columns m
+        __builtin_amdgcn_s_setprio(0);
+        plain_barrier();
     };
 
-    if constexpr (kDirect) {
-        // Sub-tile s of A (B^T): rows 64 s .. +63 of the tile's rows (columns),
-        // the step's 64 k; one 1 KiB load instruction per wave and sub-tile.
-        DmaPlan<64, 64, T::NW> plan_a, plan_b;
-        plan_a.init(lda, wave, lane);
-        plan_b.init(ldb, wave, lane);
-        const uint16_t *ga = A + static_cast<long long>(m0) * lda + kbeg;
-        const uint16_t *gb = B + static_cast<long long>(n0) * ldb + kbeg;
-        constexpr int kNoClamp = 0x7fffffff;  // every tile lies inside the matrices
-        auto dma = [&](int kt, uint16_t *stage) __attribute__((always_inline)) {
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                plan_a.issue(stage + s * T::SUB, ga + kt * T::BK, lda, 64 * s, kNoClamp, wave,
-                             lane);
-                plan_b.issue(stage + T::HALF + s * T::SUB, gb + kt * T::BK, ldb, 64 * s,
-                             kNoClamp, wave, lane);
-            }
-        };
-        dma(0, lds);
-        wait_vmem();
-        __syncthreads();
-        for (int kt = 0; kt < nkt; ++kt) {
-            if (kt + 1 < nkt)
-                dma(kt + 1, lds + ((kt + 1) & 1) * 2 * T::HALF);
-            compute(lds + (kt & 1) * 2 * T::HALF);
-            wait_vmem();
-            __syncthreads();
+    // One K step from stage S.  MODE 0: also starts the loads of the step
+    // after the next one; 1, 2: the last step but one, the last step.
+    auto step = [&](auto stage, auto mode) __attribute__((always_inline)) {
+        constexpr int S = decltype(stage)::value, MODE = decltype(mode)::value;
+        read_b(b0, 0, S);
+        if constexpr (MODE == 0)
+            load_a(0, S, pa);
+        wait_and_barrier<MODE == 0 ? 12 : MODE == 1 ? 10 : 2>();
+        products(acc[0][0], a0, b0);
+        read_b(b1, 1, S);
+        if constexpr (MODE == 0)
+            load_b(0, S, pb);
+        wait_and_barrier<MODE == 0 ? 12 : MODE == 1 ? 8 : 0>();
+        products(acc[0][1], a0, b1);
+        read_a(a1, 1, S);
+        if constexpr (MODE == 0)
+            load_b(1, S, pb);
+        wait_and_barrier<MODE == 0 ? 12 : MODE == 1 ? 6 : 0>();
+        products(acc[1][1], a1, b1);
+        if constexpr (MODE != 2)
+            read_a(a0, 0, 1 - S);
+        if constexpr (MODE == 0) {
+            load_a(1, S, pa);
+            pa += ka;
+            pb += kb;
         }
-    } else {
-        load(0);
-        store(lds);
-        __syncthreads();
-        for (int kt = 0; kt < nkt; ++kt) {
-            const bool more = kt + 1 < nkt;
-            if (more)
-                load(kt + 1);
-            compute(lds + (kt & 1) * 2 * T::HALF);
-            if (more)
-                store(lds + ((kt + 1) & 1) * 2 * T::HALF);
-            __syncthreads();
-        }
-    }
+        wait_and_barrier<MODE == 0 ? 12 : MODE == 1 ? 4 : 0>();
+        products(acc[1][0], a1, b0);
+    };
 
-    // Accumulator (i, j), register 4 q + e: column m = 32 i + l32 of the
-    // wave's rows, row n = 32 j + 8 q + 4 g + e of its columns.
+    // The loop takes K steps in pairs; an odd count starts with a step of
+    // zeros in stage 0.
+    if (nkt & 1) {
+#pragma unroll
+        for (int x = 0; x < 8; ++x)
+            *reinterpret_cast<u32x4 *>(lds + (x >> 2) * T::SIDE + ((x >> 1) & 1) * 2 * T::HALF +
+                                       (x & 1) * T::SUB + tid * 8) = u32x4{};
+    } else {
+        load_a(0, 0, pa);
+        load_b(0, 0, pb);
+        load_b(1, 0, pb);
+        load_a(1, 0, pa);
+        pa += ka;
+        pb += kb;
+    }
+    load_a(0, 1, pa);
+    load_b(0, 1, pb);
+    load_b(1, 1, pb);
+    load_a(1, 1, pa);
+    pa += ka;
+    pb += kb;
+    wait_and_barrier<8>();
+    read_a(a0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    // The second group of four waves runs half a phase behind the first: on
+    // every SIMD one wave issues products while the other reads and loads.
+    if (wm == 1)
+        plain_barrier();
+    for (int kt = 2; kt < nkt; kt += 2) {
+        step(IC<0>{}, IC<0>{});
+        step(IC<1>{}, IC<0>{});
+    }
+    step(IC<0>{}, IC<1>{});
+    step(IC<1>{}, IC<2>{});
+    if (wm == 0)
+        plain_barrier();
+
+    // Accumulator (ha, hb, i, j), register e: row m = 128 ha + 64 wm + 16 i +
+    // l16, column n = 128 hb + 32 wn + 16 j + 4 g + e of the tile.
     if constexpr (PART) {
         float *dst = P + static_cast<long long>(blockIdx.y) * M * N;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const long long m = m0 + 128 * wm + 32 * i + l32;
+        for (int x = 0; x < 16; ++x) {
+            const int ha = x >> 3, i = (x >> 1) & 3, hb = x & 1;
+            const long long m = m0 + 128 * ha + 64 * wm + 16 * i + l16;
 #pragma unroll
             for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int n = n0 + 64 * wn + 32 * j + 8 * q + 4 * g;
-                    f32x4 v;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        v[e] = acc[i][j][4 * q + e];
-                    *reinterpret_cast<f32x4 *>(dst + m * N + n) = v;
-                }
+                *reinterpret_cast<f32x4 *>(dst + m * N + n0 + 128 * hb + 32 * wn + 16 * j + 4 * g) =
+                    acc[ha][hb][i][j];
         }
     } else {
         // The tile in bf16 through LDS, then to memory in 16-byte pieces of
-        // rows.  Rows 0..127 (waves wm = 0) go to stage 0, rows 128..255 to
-        // stage 1, each 128 x 256 elements; the 4-element group n/4 of row r
-        // is stored at group (n/4) ^ (2 (r mod 16)), which keeps the two
-        // groups of a 16-byte piece adjacent and spreads one write
-        // instruction's 32 rows over the LDS banks.
-        uint16_t *ct = lds + wm * 2 * T::HALF;
+        // rows.  The 4-element group n/4 of row r is stored at group
+        // (n/4) ^ (2 (r mod 16)), which keeps the two groups of a 16-byte
+        // piece adjacent and spreads one write instruction's 16 rows over
+        // the LDS banks.
+        __syncthreads();
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int r = 32 * i + l32;
+        for (int x = 0; x < 16; ++x) {
+            const int ha = x >> 3, i = (x >> 1) & 3, hb = x & 1;
+            const int r = 128 * ha + 64 * wm + 16 * i + l16;
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int n = 64 * wn + 32 * j + 8 * q + 4 * g;
-                    *reinterpret_cast<bf16x4 *>(ct + r * T::BN + 4 * ((n >> 2) ^ (2 * (r & 15)))) =
-                        pack4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2],
-                              acc[i][j][4 * q + 3]);
-                }
+            for (int j = 0; j < 2; ++j) {
+                const int n = 128 * hb + 32 * wn + 16 * j + 4 * g;
+                const f32x4 v = acc[ha][hb][i][j];
+                *reinterpret_cast<bf16x4 *>(lds + r * T::BN + 4 * ((n >> 2) ^ (2 * (r & 15)))) =
+                    pack4(v[0], v[1], v[2], v[3]);
+            }
         }
         __syncthreads();
 #pragma unroll 4
         for (int it = 0; it < T::BM * T::BN / 8 / (64 * T::NW); ++it) {
             const int idx = it * 64 * T::NW + tid;
-            const int h = idx >> 12, r = (idx >> 5) & 127, ch = idx & 31;
-            const uint16_t *src = lds + h * 2 * T::HALF + r * T::BN + 8 * (ch ^ (r & 15));
-            const long long at = (m0 + 128 * h + r) * ldc + n0 + ch * 8;
+            const int r = idx >> 5, ch = idx & 31;
+            const uint16_t *src = lds + r * T::BN + 8 * (ch ^ (r & 15));
+            const long long at = (m0 + r) * ldc + n0 + ch * 8;
             u32x4 v = *reinterpret_cast<const u32x4 *>(src);
             if (R != nullptr) {
                 const bf16x8 x = as_bf16x8(v), y = as_bf16x8(*reinterpret_cast<const u32x4 *>(R + at));
@@ -350,12 +410,15 @@ gemm_reduce_kernel(const float *__restrict__ P, uint16_t *C, const uint16_t *R, 
 #define DD_GEMM_ARGS                                                                             \
     const uint16_t *__restrict__, const uint16_t *__restrict__, uint16_t *, float *__restrict__, \
         const uint16_t *, int, int, int, long long, long long, long long, int
-template __global__ void gemm_kernel<false, false, false>(DD_GEMM_ARGS);
-template __global__ void gemm_kernel<false, true, false>(DD_GEMM_ARGS);
-template __global__ void gemm_kernel<true, false, false>(DD_GEMM_ARGS);
-template __global__ void gemm_kernel<true, false, true>(DD_GEMM_ARGS);
-template __global__ void gemm_kernel<false, false, true>(DD_GEMM_ARGS);
-template __global__ void gemm_kernel<false, true, true>(DD_GEMM_ARGS);
+#define DD_GEMM_INST(TA, TB)                                                                     \
+    template __global__ void gemm_kernel<TA, TB, false, false>(DD_GEMM_ARGS);                    \
+    template __global__ void gemm_kernel<TA, TB, true, false>(DD_GEMM_ARGS);                     \
+    template __global__ void gemm_kernel<TA, TB, false, true>(DD_GEMM_ARGS);                     \
+    template __global__ void gemm_kernel<TA, TB, true, true>(DD_GEMM_ARGS)
+DD_GEMM_INST(false, false);
+DD_GEMM_INST(false, true);
+DD_GEMM_INST(true, false);
+#undef DD_GEMM_INST
 #undef DD_GEMM_ARGS
 
 // Splits of the K axis: enough workgroups to cover every CU about twice
@@ -388,19 +451,19 @@ int launch_gemm(const GemmArgs &a)
     uint16_t *C = static_cast<uint16_t *>(a.C);
     float *P = static_cast<float *>(a.workspace);
     const uint16_t *R = static_cast<const uint16_t *>(a.R);
-    hipError_t e;
     const bool part = splits > 1;
-#define DD_GEMM_LAUNCH(TA, TB, PT)                                                               \
-    e = launch_kernel(gemm_kernel<TA, TB, PT>, grid, dim3(512), st, A, B, C, P, R, a.M, a.N,     \
-                      a.K, a.lda, a.ldb, a.ldc, k_len)
-    if (!a.trans_a && !a.trans_b) {
-        if (part) DD_GEMM_LAUNCH(false, false, true); else DD_GEMM_LAUNCH(false, false, false);
-    } else if (!a.trans_a && a.trans_b) {
-        if (part) DD_GEMM_LAUNCH(false, true, true); else DD_GEMM_LAUNCH(false, true, false);
-    } else {
-        if (part) DD_GEMM_LAUNCH(true, false, true); else DD_GEMM_LAUNCH(true, false, false);
-    }
-#undef DD_GEMM_LAUNCH
+    const bool wide = a.lda >= kGemmWideStride || a.ldb >= kGemmWideStride;
+    auto pick = [&](auto ta, auto tb) {
+        constexpr bool TA = decltype(ta)::value, TB = decltype(tb)::value;
+        if (wide)
+            return part ? gemm_kernel<TA, TB, true, true> : gemm_kernel<TA, TB, false, true>;
+        return part ? gemm_kernel<TA, TB, true, false> : gemm_kernel<TA, TB, false, false>;
+    };
+    const auto kern = a.trans_a   ? pick(IC<1>{}, IC<0>{})
+                      : a.trans_b ? pick(IC<0>{}, IC<1>{})
+                                  : pick(IC<0>{}, IC<0>{});
+    hipError_t e = launch_kernel(kern, grid, dim3(512), st, A, B, C, P, R, a.M, a.N, a.K, a.lda,
+                                 a.ldb, a.ldc, k_len);
     if (e != hipSuccess || !part)
         return e == hipSuccess ? DD_OK : DD_ERR_HIP;
     const long long MN = static_cast<long long>(a.M) * a.N;

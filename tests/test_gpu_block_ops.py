@@ -58,6 +58,38 @@ def test_gemm(cuda, M, N, K, ta, tb):
     assert err <= RTOL
 
 
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
+@pytest.mark.parametrize("K", [64, 128, 192, 256, 320])
+def test_gemm_short_reductions(cuda, K, ta, tb):
+    # 1 to 5 K steps: the pipelined loop's first, last and odd steps
+    M, N = 256, 512
+    a = bf16((K, M) if ta else (M, K), K + 1)
+    b = bf16((N, K) if tb else (K, N), K + 2)
+    c = ops.gemm(a.to(cuda), b.to(cuda), bool(ta), bool(tb))
+    ref = f64(a.t() if ta else a) @ f64(b.t() if tb else b)
+    assert rel_l2(f64(c), ref) <= RTOL
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
+def test_gemm_wide_row_strides(cuda, ta, tb):
+    # Row strides from which eight rows no longer fit 32-bit byte offsets, on
+    # the operand with 64 rows (34 GB, of which 64 rows are used); A B^T has
+    # none with so few, its A is 2^25 elements a row (17 GB).
+    M, N, K = 256, 256, 64
+    ld = (1 << (25 if tb else 28)) + 8
+    a = bf16((K, M) if ta else (M, K), 1)
+    b = bf16((N, K) if tb else (K, N), 2)
+    narrow = (a if ta or tb else b)
+    rows, cols = narrow.shape
+    flat = torch.empty((rows - 1) * ld + cols, dtype=torch.bfloat16, device=cuda)
+    wide = flat.as_strided((rows, cols), (ld, 1))
+    wide.copy_(narrow.to(cuda))
+    A, Bm = (wide, b.to(cuda)) if ta or tb else (a.to(cuda), wide)
+    c = ops.gemm(A, Bm, bool(ta), bool(tb))
+    ref = f64(a.t() if ta else a) @ f64(b.t() if tb else b)
+    assert rel_l2(f64(c), ref) <= RTOL
+
+
 def test_gemm_strided_slices_and_residual(cuda):
     # Column slices of wider matrices as operands and output (row strides
     # passed through), and the residual added in place.
