@@ -275,7 +275,7 @@ size_t dd_gemm_workspace_bytes(int M, int N, int K)
 {
     if (M < 256 || N < 256 || K < 64 || M % 256 || N % 256 || K % 64)
         return 0;
-    return dd::gemm_workspace_bytes(M, N, K, dd::gemm_splits(M, N, K));
+    return dd::gemm_workspace_bytes(M, N, K);
 }
 
 int dd_gemm(const void *A, long long lda, int trans_a, const void *B, long long ldb, int trans_b,
@@ -293,8 +293,7 @@ int dd_gemm(const void *A, long long lda, int trans_a, const void *B, long long 
     if (lda % 8 || ldb % 8 || ldc % 8 || !aligned(A, 16) || !aligned(B, 16) || !aligned(C, 16) ||
         (R && !aligned(R, 16)))
         return DD_ERR_ALIGN;
-    const int splits = dd::gemm_splits(M, N, K);
-    const size_t need = dd::gemm_workspace_bytes(M, N, K, splits);
+    const size_t need = dd::gemm_workspace_bytes(M, N, K);
     if (need && (!workspace || workspace_bytes < need))
         return DD_ERR_WORKSPACE;
     if (need && !aligned(workspace, 16))
@@ -307,8 +306,7 @@ int dd_gemm(const void *A, long long lda, int trans_a, const void *B, long long 
     if (overlaps(rc, ra) || overlaps(rc, rb) || overlaps(rw, ra) || overlaps(rw, rb) ||
         overlaps(rw, rc) || overlaps(rw, rr) || (R && R != C && overlaps(rr, rc)))
         return DD_ERR_ALIAS;
-    dd::GemmArgs a{A, B, C, R, lda, ldb, ldc, M, N, K, trans_a != 0, trans_b != 0, splits,
-                   workspace, stream};
+    dd::GemmArgs a{A, B, C, R, lda, ldb, ldc, M, N, K, trans_a != 0, trans_b != 0, workspace, stream};
     return dd::launch_gemm(a);
 }
 

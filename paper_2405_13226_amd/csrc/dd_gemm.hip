@@ -57,6 +57,7 @@
 #include "dd_attn.h"
 
 #include <algorithm>
+#include <cmath>
 
 namespace dd {
 
@@ -94,6 +95,22 @@ __device__ __forceinline__ int row_swz(int r) { return (r >> 1) & 7; }
 __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c)
 {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+// Eight bf16 values from LDS to C + at, with R's added first if given.
+__device__ __forceinline__ void store_piece(const uint16_t *src, uint16_t *C, const uint16_t *R,
+                                            long long at)
+{
+    u32x4 v = *reinterpret_cast<const u32x4 *>(src);
+    if (R != nullptr) {
+        const bf16x8 x = as_bf16x8(v), y = as_bf16x8(*reinterpret_cast<const u32x4 *>(R + at));
+        bf16x8 z;
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+            z[t] = static_cast<__bf16>(static_cast<float>(x[t]) + static_cast<float>(y[t]));
+        v = __builtin_bit_cast(u32x4, z);
+    }
+    *reinterpret_cast<u32x4 *>(C + at) = v;
 }
 
 // Row strides (elements) from which a load's per-lane byte offset, up to 7
@@ -363,16 +380,204 @@ gemm_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint
             const int r = idx >> 5, ch = idx & 31;
             const uint16_t *src = lds + r * T::BN + 8 * (ch ^ (r & 15));
             const long long at = (m0 + r) * ldc + n0 + ch * 8;
-            u32x4 v = *reinterpret_cast<const u32x4 *>(src);
-            if (R != nullptr) {
-                const bf16x8 x = as_bf16x8(v), y = as_bf16x8(*reinterpret_cast<const u32x4 *>(R + at));
-                bf16x8 z;
+            store_piece(src, C, R, at);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The 128 x 128 tile, for products whose 256 x 256 tiles would leave CUs
+// idle.  Eight waves, wave (wm, wn) owning rows 64 wm .. +63 and columns
+// 32 wn .. +31: one phase of 16 products per K step.  With one workgroup per
+// CU nothing else hides a load's latency, so four stages (128 KiB) hold the
+// step being read and three in flight (three or five measured the same or
+// slower); the two groups of four waves run half a phase apart as in the
+// large kernel.
+//
+// What bounds the loop: the LDS.  A step reads 96 KiB and receives 32 KiB,
+// 1024 clocks at 128 bytes each; it takes 0.41 us (0.86 us of products per
+// 256 x 256 step, a quarter of that here).  Reading 64 KiB instead (each
+// group of four waves taking half of the step's k for the whole tile, the
+// two sums added at the end) measured 6% faster at K = 5632 and 5% slower at
+// K = 1024.  2048 x 1024 x 1024: 21.1 us on 32 large tiles, 11.4-12.6 here.
+struct GemmSmallTile {
+    static constexpr int BM = 128, BN = 128, BK = 64, NW = 8, NST = 4;
+    static constexpr int SUB = 64 * 64;
+    static constexpr int STAGE = 4 * SUB;  // A sub-tiles 0, 1, B sub-tiles 0, 1
+};
+
+template <bool TA, bool TB, bool PART, bool WIDE>
+__global__ void __launch_bounds__(512, 1)
+gemm_small_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint16_t *C,
+                  float *__restrict__ P, const uint16_t *R, int M, int N, int K, long long lda,
+                  long long ldb, long long ldc, int k_len)
+{
+    using T = GemmSmallTile;
+    __shared__ __attribute__((aligned(1024))) uint16_t lds[T::NST * T::STAGE];
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int l16 = lane & 15, g = lane >> 4;
+    const int wm = wave >> 2, wn = wave & 3;
+    // Tile rows x, x + 8, ... on XCD x where the rows divide over the XCDs.
+    const int tiles_m = M / T::BM, tiles_n = N / T::BN;
+    int tm, tn;
+    if (gridDim.y == 1 && tiles_m % kXcds == 0) {
+        const int x = static_cast<int>(blockIdx.x) % kXcds, k = static_cast<int>(blockIdx.x) / kXcds;
+        const int rows_x = tiles_m / kXcds;
+        tm = (k % rows_x) * kXcds + x;
+        tn = k / rows_x;
+    } else {
+        tm = static_cast<int>(blockIdx.x) / tiles_n;
+        tn = static_cast<int>(blockIdx.x) % tiles_n;
+    }
+    const int m0 = tm * T::BM, n0 = tn * T::BN;
+    const int kbeg = static_cast<int>(blockIdx.y) * k_len;
+    const int nkt = min(k_len, K - kbeg) / T::BK;
+
+    const int qr = lane >> 3, qrow = 8 * wave + qr;
+    const int xa = ((lane & 7) ^ (TA ? swz<64>(qrow) : row_swz(qrow))) * 8;
+    const int xb = ((lane & 7) ^ (TB ? row_swz(qrow) : swz<64>(qrow))) * 8;
+    const long long va = (qr * lda + xa) * 2, vb = (qr * ldb + xb) * 2;  // bytes
+    const uint16_t *pa = A + 8 * wave * lda +
+                         (TA ? static_cast<long long>(kbeg) * lda + m0 : static_cast<long long>(m0) * lda + kbeg);
+    const uint16_t *pb = B + 8 * wave * ldb +
+                         (TB ? static_cast<long long>(n0) * ldb + kbeg : static_cast<long long>(kbeg) * ldb + n0);
+    const long long sa = TA ? 64 : 64 * lda, sb = TB ? 64 * ldb : 64;
+    const long long ka = TA ? 64 * lda : 64, kb = TB ? 64 : 64 * ldb;
+    const uint32_t lds0 = lds_base_sgpr(lds) + 1024u * wave;
+    auto load = [&](const uint16_t *p, long long v, uint32_t l) __attribute__((always_inline)) {
+        if constexpr (WIDE)
+            dma_b128(reinterpret_cast<const char *>(p) + v, l);
+        else
+            dma_b128_off(p, static_cast<uint32_t>(v), l);
+    };
+    // The K step that pa and pb point at, into stage st; moves them on.
+    auto load_step = [&](int st) __attribute__((always_inline)) {
+        const uint32_t l = lds0 + 2u * T::STAGE * st;
+        load(pa, va, l);
+        load(pb, vb, l + 4u * T::SUB);
+        load(pa + sa, va, l + 2u * T::SUB);
+        load(pb + sb, vb, l + 6u * T::SUB);
+        pa += ka;
+        pb += kb;
+    };
+
+    const int e4 = l16 >> 2, c4 = l16 & 3;
+    int fa[TA ? 8 : 2], fb[TB ? 2 : 4];  // element offsets in a stage
+    {
+        const int as = wm * T::SUB, bs = (2 + (wn >> 1)) * T::SUB;
+        if constexpr (TA) {
 #pragma unroll
-                for (int t = 0; t < 8; ++t)
-                    z[t] = static_cast<__bf16>(static_cast<float>(x[t]) + static_cast<float>(y[t]));
-                v = __builtin_bit_cast(u32x4, z);
+            for (int i = 0; i < 8; ++i)
+                fa[i] = as + tile_off<64>(8 * g + 4 * (i & 1) + e4, 16 * (i >> 1) + 4 * c4);
+        } else {
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk)
+                fa[kk] = as + 64 * l16 + (((4 * kk + g) ^ row_swz(l16)) << 3);
+        }
+        if constexpr (TB) {
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk)
+                fb[kk] = bs + 64 * (32 * (wn & 1) + l16) + (((4 * kk + g) ^ row_swz(l16)) << 3);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                fb[j] = bs + tile_off<64>(8 * g + 4 * (j & 1) + e4,
+                                          32 * (wn & 1) + 16 * (j >> 1) + 4 * c4);
+        }
+    }
+    f32x4 acc[4][2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            acc[i][j] = f32x4{};
+
+    const int first = min(nkt, T::NST - 1);
+    for (int kt = 0; kt < first; ++kt)
+        load_step(kt);
+    if (nkt > 2)
+        wait_and_barrier<8>();
+    else
+        wait_and_barrier<0>();
+    if (wm == 1)
+        plain_barrier();
+    for (int kt = 0; kt < nkt; ++kt) {
+        const uint16_t *st = lds + (kt % T::NST) * T::STAGE;
+        bf16x8 a[4][2], b[2][2];
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                if constexpr (TB)
+                    b[j][kk] = lds_row8(st + fb[kk] + 1024 * j);
+                else
+                    b[j][kk] = join(lds_tr4(st + fb[2 * j] + 2048 * kk),
+                                    lds_tr4(st + fb[2 * j + 1] + 2048 * kk));
             }
-            *reinterpret_cast<u32x4 *>(C + at) = v;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if constexpr (TA)
+                    a[i][kk] = join(lds_tr4(st + fa[2 * i] + 2048 * kk),
+                                    lds_tr4(st + fa[2 * i + 1] + 2048 * kk));
+                else
+                    a[i][kk] = lds_row8(st + fa[kk] + 1024 * i);
+            }
+        }
+        // The stage that the step before has read takes the step three ahead;
+        // the next step has to be there (the two after it may be in flight).
+        if (kt + 3 < nkt) {
+            load_step((kt + 3) % T::NST);
+            wait_and_barrier<8>();
+        } else if (kt + 2 < nkt) {
+            wait_and_barrier<4>();
+        } else {
+            wait_and_barrier<0>();
+        }
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = mfma16(b[j][kk], a[i][kk], acc[i][j]);  // rows n, columns m
+        __builtin_amdgcn_s_setprio(0);
+        plain_barrier();
+    }
+    if (wm == 0)
+        plain_barrier();
+
+    // Accumulator (i, j), register e: row m = 64 wm + 16 i + l16, column
+    // n = 32 wn + 16 j + 4 g + e of the tile; stored as in the large kernel.
+    if constexpr (PART) {
+        float *dst = P + static_cast<long long>(blockIdx.y) * M * N;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                *reinterpret_cast<f32x4 *>(dst + static_cast<long long>(m0 + 64 * wm + 16 * i + l16) * N +
+                                           n0 + 32 * wn + 16 * j + 4 * g) = acc[i][j];
+    } else {
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int r = 64 * wm + 16 * i + l16;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int n = 32 * wn + 16 * j + 4 * g;
+                const f32x4 v = acc[i][j];
+                *reinterpret_cast<bf16x4 *>(lds + r * T::BN + 4 * ((n >> 2) ^ (2 * (r & 15)))) =
+                    pack4(v[0], v[1], v[2], v[3]);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < T::BM * T::BN / 8 / (64 * T::NW); ++it) {
+            const int idx = it * 64 * T::NW + tid;
+            const int r = idx >> 4, ch = idx & 15;
+            store_piece(lds + r * T::BN + 8 * (ch ^ (r & 15)), C, R, (m0 + r) * ldc + n0 + ch * 8);
         }
     }
 }
@@ -414,37 +619,70 @@ gemm_reduce_kernel(const float *__restrict__ P, uint16_t *C, const uint16_t *R, 
     template __global__ void gemm_kernel<TA, TB, false, false>(DD_GEMM_ARGS);                    \
     template __global__ void gemm_kernel<TA, TB, true, false>(DD_GEMM_ARGS);                     \
     template __global__ void gemm_kernel<TA, TB, false, true>(DD_GEMM_ARGS);                     \
-    template __global__ void gemm_kernel<TA, TB, true, true>(DD_GEMM_ARGS)
+    template __global__ void gemm_kernel<TA, TB, true, true>(DD_GEMM_ARGS);                      \
+    template __global__ void gemm_small_kernel<TA, TB, false, false>(DD_GEMM_ARGS);              \
+    template __global__ void gemm_small_kernel<TA, TB, true, false>(DD_GEMM_ARGS);               \
+    template __global__ void gemm_small_kernel<TA, TB, false, true>(DD_GEMM_ARGS);               \
+    template __global__ void gemm_small_kernel<TA, TB, true, true>(DD_GEMM_ARGS)
 DD_GEMM_INST(false, false);
 DD_GEMM_INST(false, true);
 DD_GEMM_INST(true, false);
 #undef DD_GEMM_INST
 #undef DD_GEMM_ARGS
 
-// Splits of the K axis: enough workgroups to cover every CU about twice
-// (tiles alone leave CUs idle when M N / 256^2 is small and K is long), each
-// split a multiple of 64 and at least 1024 long.
-int gemm_splits(int M, int N, int K)
+// Estimated time (us) of a product on tiles of `edge` with `splits` K parts:
+// rounds of workgroups over the CUs (one per CU), each a start-up and tail
+// plus its K steps, then the partial sums' write and read.  The constants
+// are fits to graph-replayed products: 2048 x 1024 at K = 1024 / 2816 / 5632
+// takes 21 / 46 / 85 us on large tiles and 12.6 / 26 / 42 on small ones;
+// with two splits 28 / 38 / 57 and 17 / 26 / 40; a chip full of large tiles
+// runs slower (1.4 us a step) for its power.
+static double gemm_cost(double tiles, double cus, double steps, double splits, double mn,
+                        bool small)
 {
-    const long long tiles = static_cast<long long>(M / GemmTile::BM) * (N / GemmTile::BN);
-    const int cus = std::max(device_cu_count(), 1);
-    int s = 1;
-    while (tiles * s < 2LL * cus && K / (2 * s) >= 1024 && (K / (2 * s)) % GemmTile::BK == 0)
-        s *= 2;
-    return s;
+    const double wgs = tiles * splits, rounds = std::ceil(wgs / cus);
+    const double step = small ? 0.42 : wgs < cus ? 1.02 + 0.2 * wgs / cus : 1.4;
+    const double reduce = splits > 1 ? 6.0 + splits * mn * 8.0 / 4.0e6 : 0.0;
+    return rounds * (std::ceil(steps / splits) * step + (small ? 5.5 : 6.0)) + reduce;
 }
 
-size_t gemm_workspace_bytes(int M, int N, int K, int splits)
+// The cheapest of large or small tiles and 1, 2, 4, ... K splits.  Splits
+// are multiples of 64 and at least 1024 long, and more of them than two
+// large tiles per CU are never needed.
+GemmPlan gemm_plan(int M, int N, int K)
 {
-    return splits > 1 ? static_cast<size_t>(splits) * M * N * sizeof(float) : 0;
+    const int cus = std::max(device_cu_count(), 1);
+    const long long tiles = static_cast<long long>(M / GemmTile::BM) * (N / GemmTile::BN);
+    GemmPlan best{false, 1};
+    double cost = -1;
+    for (int s = 1;; s *= 2) {
+        for (const bool small : {false, true}) {
+            const double c = gemm_cost(static_cast<double>(small ? 4 * tiles : tiles), cus,
+                                       K / 64.0, s, static_cast<double>(M) * N, small);
+            if (cost < 0 || c < cost) {
+                cost = c;
+                best = GemmPlan{small, s};
+            }
+        }
+        if (tiles * s >= 2LL * cus || K / (2 * s) < 1024 || (K / (2 * s)) % GemmTile::BK != 0)
+            return best;
+    }
+}
+
+size_t gemm_workspace_bytes(int M, int N, int K)
+{
+    const GemmPlan p = gemm_plan(M, N, K);
+    return p.splits > 1 ? static_cast<size_t>(p.splits) * M * N * sizeof(float) : 0;
 }
 
 int launch_gemm(const GemmArgs &a)
 {
     hipStream_t st = static_cast<hipStream_t>(a.stream);
-    const int splits = a.splits;
+    const GemmPlan plan = gemm_plan(a.M, a.N, a.K);
+    const int splits = plan.splits;
     const int k_len = a.K / splits;
-    const dim3 grid(static_cast<unsigned>((a.M / GemmTile::BM) * (a.N / GemmTile::BN)),
+    const int edge = plan.small ? GemmSmallTile::BM : GemmTile::BM;
+    const dim3 grid(static_cast<unsigned>((a.M / edge) * (a.N / edge)),
                     static_cast<unsigned>(splits));
     const uint16_t *A = static_cast<const uint16_t *>(a.A);
     const uint16_t *B = static_cast<const uint16_t *>(a.B);
@@ -455,6 +693,13 @@ int launch_gemm(const GemmArgs &a)
     const bool wide = a.lda >= kGemmWideStride || a.ldb >= kGemmWideStride;
     auto pick = [&](auto ta, auto tb) {
         constexpr bool TA = decltype(ta)::value, TB = decltype(tb)::value;
+        if (plan.small) {
+            if (wide)
+                return part ? gemm_small_kernel<TA, TB, true, true>
+                            : gemm_small_kernel<TA, TB, false, true>;
+            return part ? gemm_small_kernel<TA, TB, true, false>
+                        : gemm_small_kernel<TA, TB, false, false>;
+        }
         if (wide)
             return part ? gemm_kernel<TA, TB, true, true> : gemm_kernel<TA, TB, false, true>;
         return part ? gemm_kernel<TA, TB, true, false> : gemm_kernel<TA, TB, false, false>;

@@ -72,12 +72,17 @@ struct GemmArgs {
     long long lda, ldb, ldc;  // row strides in elements
     int M, N, K;
     bool trans_a, trans_b;    // A stored [K][M]; B stored [N][K] (not both)
-    int splits;               // K splits (1: none); > 1 needs the workspace
-    void *workspace;          // fp32 [splits][M][N]
+    void *workspace;          // fp32 [splits][M][N] of gemm_plan, if it splits
     void *stream;
 };
-int gemm_splits(int M, int N, int K);
-size_t gemm_workspace_bytes(int M, int N, int K, int splits);
+// How a product of these sizes runs: on 256 x 256 or (small) 128 x 128 tiles,
+// with the K axis in `splits` parts (1: none; more need the workspace).
+struct GemmPlan {
+    bool small;
+    int splits;
+};
+GemmPlan gemm_plan(int M, int N, int K);
+size_t gemm_workspace_bytes(int M, int N, int K);
 int launch_gemm(const GemmArgs &a);
 
 // LayerNorm over rows of d elements (dd_block.hip), d in {512, 1024, 2048}.

@@ -60,9 +60,9 @@ def test_gemm(cuda, M, N, K, ta, tb):
 
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
 @pytest.mark.parametrize("K", [64, 128, 192, 256, 320])
-def test_gemm_short_reductions(cuda, K, ta, tb):
-    # 1 to 5 K steps: the pipelined loop's first, last and odd steps
-    M, N = 256, 512
+@pytest.mark.parametrize("M,N", [(256, 512), (2048, 8192)])  # small tiles; one large tile per CU
+def test_gemm_short_reductions(cuda, M, N, K, ta, tb):
+    # 1 to 5 K steps: the pipelined loops' first, last and odd steps
     a = bf16((K, M) if ta else (M, K), K + 1)
     b = bf16((N, K) if tb else (K, N), K + 2)
     c = ops.gemm(a.to(cuda), b.to(cuda), bool(ta), bool(tb))
