@@ -208,6 +208,33 @@ int dd_gemm(const void *A, long long lda, int trans_a, const void *B, long long 
 size_t dd_gemm_workspace_bytes(int M, int N, int K); /* 0: none needed, or invalid */
 
 /*
+ * Products of the block that share an operand or a result, one launch each;
+ * conditions as for dd_gemm, n from 1 to 3:
+ *   dd_gemm_group  C[i] = op(A) op(B[i]), i < n (the q, k, v projections;
+ *                  weight gradients of projections with one input); the C[i]
+ *                  may be column slices of one matrix.  workspace:
+ *                  dd_gemm_group_workspace_bytes(M, N, K, n).
+ *   dd_gemm_sum    C = sum over i < n of A[i] op(B[i]) (the gradient of an
+ *                  input of several projections), one fp32 sum, no workspace.
+ *   dd_gemm_swiglu U = X W1, V = X W3, Y = silu(U) * V of the rounded values
+ *                  (the gated half of the MLP; U, V, Y with row stride ldy).
+ *   dd_gemm_swiglu_bwd  dU, dV = gradients of silu(U) * V for the upstream
+ *                  gradient dY W^T, rounded to bf16 (W stored [N][K]; U, V,
+ *                  dU, dV with row stride ldu).
+ */
+int dd_gemm_group(const void *A, long long lda, int trans_a, const void *const *B, long long ldb,
+                  int trans_b, void *const *C, long long ldc, int n, int M, int N, int K,
+                  void *workspace, size_t workspace_bytes, void *stream);
+size_t dd_gemm_group_workspace_bytes(int M, int N, int K, int n);
+int dd_gemm_sum(const void *const *A, long long lda, const void *const *B, long long ldb,
+                int trans_b, void *C, long long ldc, int n, int M, int N, int K, void *stream);
+int dd_gemm_swiglu(const void *X, long long ldx, const void *W1, const void *W3, long long ldw,
+                   void *U, void *V, void *Y, long long ldy, int M, int N, int K, void *stream);
+int dd_gemm_swiglu_bwd(const void *dY, long long ldy, const void *W, long long ldw, const void *U,
+                       const void *V, void *dU, void *dV, long long ldu, int M, int N, int K,
+                       void *stream);
+
+/*
  * LayerNorm over the rows of X [rows, d] (bf16, d in {512, 1024, 2048}):
  * Y = (X - mean) / sqrt(var + eps) * w + b with the biased variance of the
  * row; w, b: bf16 [d]; mean, rstd: fp32 [rows] outputs kept for the

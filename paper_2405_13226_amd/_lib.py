@@ -12,7 +12,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libdd_attn.so")
 
 # name -> (restype, argtypes); mirrors include/dd_attn.h
-_P, _I, _F = ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p
+_P, _I, _F, _L = ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p, ctypes.c_longlong
 SIGNATURES = {
     "dd_attn_fwd": (ctypes.c_int, [_P, _P, _P, _P, _F, _I, _I, _I, _I, _I, _P, _I, _P]),
     "dd_attn_bwd": (ctypes.c_int, [_P, _P, _P, _P, _P, _F, _P, _P, _P, _I, _I, _I, _I, _I,
@@ -28,6 +28,12 @@ SIGNATURES = {
     "dd_gemm": (ctypes.c_int, [_P, ctypes.c_longlong, _I, _P, ctypes.c_longlong, _I, _P, _P,
                                ctypes.c_longlong, _I, _I, _I, _P, ctypes.c_size_t, _P]),
     "dd_gemm_workspace_bytes": (ctypes.c_size_t, [_I, _I, _I]),
+    "dd_gemm_group": (ctypes.c_int, [_P, _L, _I, _P, _L, _I, _P, _L, _I, _I, _I, _I, _P,
+                                     ctypes.c_size_t, _P]),
+    "dd_gemm_group_workspace_bytes": (ctypes.c_size_t, [_I, _I, _I, _I]),
+    "dd_gemm_sum": (ctypes.c_int, [_P, _L, _P, _L, _I, _P, _L, _I, _I, _I, _I, _P]),
+    "dd_gemm_swiglu": (ctypes.c_int, [_P, _L, _P, _P, _L, _P, _P, _P, _L, _I, _I, _I, _P]),
+    "dd_gemm_swiglu_bwd": (ctypes.c_int, [_P, _L, _P, _L, _P, _P, _P, _P, _L, _I, _I, _I, _P]),
     "dd_layernorm_fwd": (ctypes.c_int, [_P, _P, _P, _P, _P, _P, _I, _I, ctypes.c_float, _P]),
     "dd_layernorm_bwd": (ctypes.c_int, [_P, _P, _P, _P, _P, _P, _P, _P, _P, _I, _I, _P,
                                         ctypes.c_size_t, _P]),

@@ -64,6 +64,88 @@ def gemm(a, b, trans_a: bool = False, trans_b: bool = False, residual=None, out=
     return out
 
 
+def _same(ts, name):
+    """Matrices of one shape and row stride; returns that stride."""
+    for t in ts:
+        _mat(t, name)
+        if t.shape != ts[0].shape or t.stride(0) != ts[0].stride(0):
+            raise ValueError(f"the {name} matrices must agree in shape and row stride")
+    return ts[0].stride(0)
+
+
+def _array(ts):
+    return (ctypes.c_void_p * len(ts))(*(t.data_ptr() for t in ts))
+
+
+def gemm_group(a, bs, trans_a: bool = False, trans_b: bool = False, outs=None):
+    """[op(a) @ op(b) for b in bs] in one launch (at most three of one shape)."""
+    _mat(a, "a")
+    ldb = _same(bs, "b")
+    M, K = (a.shape[1], a.shape[0]) if trans_a else (a.shape[0], a.shape[1])
+    Kb, N = (bs[0].shape[1], bs[0].shape[0]) if trans_b else (bs[0].shape[0], bs[0].shape[1])
+    if K != Kb:
+        raise ValueError(f"inner dimensions differ: {K} vs {Kb}")
+    n = len(bs)
+    if outs is None:
+        outs = [torch.empty((M, N), dtype=torch.bfloat16, device=a.device) for _ in bs]
+    ldc = _same(outs, "out")
+    if len(outs) != n or tuple(outs[0].shape) != (M, N):
+        raise ValueError(f"need {n} outputs of shape {(M, N)}")
+    need = lib().dd_gemm_group_workspace_bytes(M, N, K, n)
+    ws = torch.empty(need, dtype=torch.uint8, device=a.device) if need else None
+    st = lib().dd_gemm_group(_p(a), a.stride(0), int(bool(trans_a)), _array(bs), ldb,
+                             int(bool(trans_b)), _array(outs), ldc, n, M, N, K, _p(ws), need,
+                             _stream(a.device))
+    check(st, "dd_gemm_group")
+    return outs
+
+
+def gemm_sum(as_, bs, trans_b: bool = False):
+    """sum of a @ op(b) over the pairs of as_ and bs (at most three), summed in
+    fp32 and rounded once."""
+    lda, ldb = _same(as_, "a"), _same(bs, "b")
+    M, K = as_[0].shape
+    Kb, N = (bs[0].shape[1], bs[0].shape[0]) if trans_b else (bs[0].shape[0], bs[0].shape[1])
+    if K != Kb or len(as_) != len(bs):
+        raise ValueError("the pairs must agree in their inner dimension")
+    out = torch.empty((M, N), dtype=torch.bfloat16, device=as_[0].device)
+    st = lib().dd_gemm_sum(_array(as_), lda, _array(bs), ldb, int(bool(trans_b)), _p(out), N,
+                           len(as_), M, N, K, _stream(out.device))
+    check(st, "dd_gemm_sum")
+    return out
+
+
+def gemm_swiglu(x, w1, w3):
+    """(u, v, silu(u) * v) with u = x @ w1 and v = x @ w3, in one launch."""
+    _mat(x, "x")
+    ldw = _same([w1, w3], "w")
+    (M, K), (Kw, N) = x.shape, w1.shape
+    if K != Kw:
+        raise ValueError(f"inner dimensions differ: {K} vs {Kw}")
+    u, v, y = (torch.empty((M, N), dtype=torch.bfloat16, device=x.device) for _ in range(3))
+    st = lib().dd_gemm_swiglu(_p(x), x.stride(0), _p(w1), _p(w3), ldw, _p(u), _p(v), _p(y), N,
+                              M, N, K, _stream(x.device))
+    check(st, "dd_gemm_swiglu")
+    return u, v, y
+
+
+def gemm_swiglu_backward(dy, w, u, v):
+    """(du, dv) of silu(u) * v for the upstream gradient dy @ w.T, in one launch."""
+    _mat(dy, "dy")
+    _mat(w, "w")
+    ldu = _same([u, v], "u")
+    (M, K), (N, Kw) = dy.shape, w.shape
+    if K != Kw or tuple(u.shape) != (M, N):
+        raise ValueError("the shapes of dy, w and u do not agree")
+    if ldu != N:
+        raise ValueError("u and v must be contiguous")
+    du, dv = torch.empty_like(u), torch.empty_like(v)
+    st = lib().dd_gemm_swiglu_bwd(_p(dy), dy.stride(0), _p(w), w.stride(0), _p(u), _p(v), _p(du),
+                                  _p(dv), N, M, N, K, _stream(dy.device))
+    check(st, "dd_gemm_swiglu_bwd")
+    return du, dv
+
+
 def transpose(x, out=None):
     """x.T as a bf16 matrix with unit column stride (into ``out`` if given)."""
     _mat(x, "x")

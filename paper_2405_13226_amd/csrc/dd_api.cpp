@@ -271,43 +271,160 @@ int dd_attn_bwd_rope(const void *Q, const void *K, const void *V, const void *O,
                             workspace, workspace_bytes, stream);
 }
 
+namespace {
+
+// Checks the shapes, strides, pointers and overlaps that every product of
+// dd::GemmArgs has (`outs` outputs, workspace already in `a`) and launches it.
+int run_gemm(dd::GemmArgs &a, int outs, size_t workspace_bytes)
+{
+    const bool swiglu = a.kind == dd::GemmArgs::kSwiglu;
+    const int n_a = a.segs, n_b = swiglu ? 2 : a.groups * a.segs;
+    for (int i = 0; i < n_a; ++i)
+        if (!a.A[i])
+            return DD_ERR_NULL;
+    for (int i = 0; i < n_b; ++i)
+        if (!a.B[i])
+            return DD_ERR_NULL;
+    for (int i = 0; i < outs; ++i)
+        if (!a.C[i])
+            return DD_ERR_NULL;
+    const int M = a.M, N = a.N, K = a.K;
+    if (M < 256 || N < 256 || K < 64 || M % 256 || N % 256 || K % 64 || (a.trans_a && a.trans_b))
+        return DD_ERR_SHAPE;
+    const long long a_rows = a.trans_a ? K : M, a_cols = a.trans_a ? M : K;
+    const long long b_rows = a.trans_b ? N : K, b_cols = a.trans_b ? K : N;
+    if (a.lda < a_cols || a.ldb < b_cols || a.ldc < N)
+        return DD_ERR_SHAPE;
+    if (a.lda % 8 || a.ldb % 8 || a.ldc % 8)
+        return DD_ERR_ALIGN;
+    const size_t cbytes = static_cast<size_t>((static_cast<long long>(M) - 1) * a.ldc + N) * 2;
+    Range ins[8];
+    int n_in = 0;
+    for (int i = 0; i < n_a; ++i)
+        ins[n_in++] = range_of(a.A[i], static_cast<size_t>((a_rows - 1) * a.lda + a_cols) * 2);
+    for (int i = 0; i < n_b; ++i)
+        ins[n_in++] = range_of(a.B[i], static_cast<size_t>((b_rows - 1) * a.ldb + b_cols) * 2);
+    for (const void *p : std::initializer_list<const void *>{a.U, a.V})
+        if (p)
+            ins[n_in++] = range_of(p, cbytes);
+    for (int i = 0; i < n_in; ++i)
+        if (ins[i].lo & 15)
+            return DD_ERR_ALIGN;
+    for (int i = 0; i < outs; ++i)
+        if (!aligned(a.C[i], 16))
+            return DD_ERR_ALIGN;
+    if (a.R && !aligned(a.R, 16))
+        return DD_ERR_ALIGN;
+    const size_t need = a.kind == dd::GemmArgs::kPlain && a.segs == 1
+                            ? dd::gemm_workspace_bytes(M, N, K, a.groups)
+                            : 0;
+    if (need && (!a.workspace || workspace_bytes < need))
+        return DD_ERR_WORKSPACE;
+    if (need && !aligned(a.workspace, 16))
+        return DD_ERR_ALIGN;
+    Range rr = range_of(a.R, a.R ? cbytes : 0), rw = range_of(a.workspace, need);
+    for (int i = 0; i < n_in; ++i)
+        if (overlaps(rw, ins[i]))
+            return DD_ERR_ALIAS;
+    if (overlaps(rw, rr))
+        return DD_ERR_ALIAS;
+    for (int i = 0; i < outs; ++i) {
+        Range rc = range_of(a.C[i], cbytes);
+        for (int j = 0; j < n_in; ++j)
+            if (overlaps(rc, ins[j]))
+                return DD_ERR_ALIAS;
+        if (overlaps(rw, rc) || (a.R && a.R != a.C[i] && overlaps(rr, rc)))
+            return DD_ERR_ALIAS;
+        // Outputs may be column slices of one matrix: they are apart if
+        // their columns are.
+        for (int j = 0; j < i; ++j) {
+            Range rd = range_of(a.C[j], cbytes);
+            if (!overlaps(rc, rd))
+                continue;
+            const long long shift = static_cast<long long>(rc.lo < rd.lo ? rd.lo - rc.lo : rc.lo - rd.lo) / 2 % a.ldc;
+            if (shift < N || shift + N > a.ldc)
+                return DD_ERR_ALIAS;
+        }
+    }
+    return dd::launch_gemm(a);
+}
+
+bool gemm_sizes_ok(int M, int N, int K)
+{
+    return M >= 256 && N >= 256 && K >= 64 && M % 256 == 0 && N % 256 == 0 && K % 64 == 0;
+}
+
+}  // namespace
+
 size_t dd_gemm_workspace_bytes(int M, int N, int K)
 {
-    if (M < 256 || N < 256 || K < 64 || M % 256 || N % 256 || K % 64)
-        return 0;
-    return dd::gemm_workspace_bytes(M, N, K);
+    return gemm_sizes_ok(M, N, K) ? dd::gemm_workspace_bytes(M, N, K, 1) : 0;
+}
+
+size_t dd_gemm_group_workspace_bytes(int M, int N, int K, int n)
+{
+    return gemm_sizes_ok(M, N, K) && n >= 1 && n <= 3 ? dd::gemm_workspace_bytes(M, N, K, n) : 0;
 }
 
 int dd_gemm(const void *A, long long lda, int trans_a, const void *B, long long ldb, int trans_b,
             const void *R, void *C, long long ldc, int M, int N, int K, void *workspace,
             size_t workspace_bytes, void *stream)
 {
-    if (!A || !B || !C)
+    dd::GemmArgs a{dd::GemmArgs::kPlain, {A}, {B}, {C}, R, nullptr, nullptr, lda, ldb, ldc, 1, 1,
+                   M, N, K, trans_a != 0, trans_b != 0, workspace, stream};
+    return run_gemm(a, 1, workspace_bytes);
+}
+
+int dd_gemm_group(const void *A, long long lda, int trans_a, const void *const *B, long long ldb,
+                  int trans_b, void *const *C, long long ldc, int n, int M, int N, int K,
+                  void *workspace, size_t workspace_bytes, void *stream)
+{
+    if (!B || !C)
         return DD_ERR_NULL;
-    if (M < 256 || N < 256 || K < 64 || M % 256 || N % 256 || K % 64 || (trans_a && trans_b))
+    if (n < 1 || n > 3)
         return DD_ERR_SHAPE;
-    const long long a_rows = trans_a ? K : M, a_cols = trans_a ? M : K;
-    const long long b_rows = trans_b ? N : K, b_cols = trans_b ? K : N;
-    if (lda < a_cols || ldb < b_cols || ldc < N)
+    dd::GemmArgs a{dd::GemmArgs::kPlain, {A}, {}, {}, nullptr, nullptr, nullptr, lda, ldb, ldc, n,
+                   1, M, N, K, trans_a != 0, trans_b != 0, workspace, stream};
+    for (int i = 0; i < n; ++i) {
+        a.B[i] = B[i];
+        a.C[i] = C[i];
+    }
+    return run_gemm(a, n, workspace_bytes);
+}
+
+int dd_gemm_sum(const void *const *A, long long lda, const void *const *B, long long ldb,
+                int trans_b, void *C, long long ldc, int n, int M, int N, int K, void *stream)
+{
+    if (!A || !B)
+        return DD_ERR_NULL;
+    if (n < 1 || n > 3)
         return DD_ERR_SHAPE;
-    if (lda % 8 || ldb % 8 || ldc % 8 || !aligned(A, 16) || !aligned(B, 16) || !aligned(C, 16) ||
-        (R && !aligned(R, 16)))
-        return DD_ERR_ALIGN;
-    const size_t need = dd::gemm_workspace_bytes(M, N, K);
-    if (need && (!workspace || workspace_bytes < need))
-        return DD_ERR_WORKSPACE;
-    if (need && !aligned(workspace, 16))
-        return DD_ERR_ALIGN;
-    Range ra = range_of(A, static_cast<size_t>((a_rows - 1) * lda + a_cols) * 2);
-    Range rb = range_of(B, static_cast<size_t>((b_rows - 1) * ldb + b_cols) * 2);
-    const size_t cbytes = static_cast<size_t>((static_cast<long long>(M) - 1) * ldc + N) * 2;
-    Range rc = range_of(C, cbytes), rr = range_of(R, R ? cbytes : 0);
-    Range rw = range_of(workspace, need);
-    if (overlaps(rc, ra) || overlaps(rc, rb) || overlaps(rw, ra) || overlaps(rw, rb) ||
-        overlaps(rw, rc) || overlaps(rw, rr) || (R && R != C && overlaps(rr, rc)))
-        return DD_ERR_ALIAS;
-    dd::GemmArgs a{A, B, C, R, lda, ldb, ldc, M, N, K, trans_a != 0, trans_b != 0, workspace, stream};
-    return dd::launch_gemm(a);
+    dd::GemmArgs a{dd::GemmArgs::kPlain, {}, {}, {C}, nullptr, nullptr, nullptr, lda, ldb, ldc, 1,
+                   n, M, N, K, false, trans_b != 0, nullptr, stream};
+    for (int i = 0; i < n; ++i) {
+        a.A[i] = A[i];
+        a.B[i] = B[i];
+    }
+    return run_gemm(a, 1, 0);
+}
+
+int dd_gemm_swiglu(const void *X, long long ldx, const void *W1, const void *W3, long long ldw,
+                   void *U, void *V, void *Y, long long ldy, int M, int N, int K, void *stream)
+{
+    dd::GemmArgs a{dd::GemmArgs::kSwiglu, {X}, {W1, W3}, {U, V, Y}, nullptr, nullptr, nullptr,
+                   ldx, ldw, ldy, 1, 1, M, N, K, false, false, nullptr, stream};
+    return run_gemm(a, 3, 0);
+}
+
+int dd_gemm_swiglu_bwd(const void *dY, long long ldy, const void *W, long long ldw, const void *U,
+                       const void *V, void *dU, void *dV, long long ldu, int M, int N, int K,
+                       void *stream)
+{
+    if (!U || !V)
+        return DD_ERR_NULL;
+    dd::GemmArgs a{dd::GemmArgs::kSwigluBackward, {dY}, {W}, {dU, dV}, nullptr, U, V, ldy, ldw,
+                   ldu, 1, 1, M, N, K, false, true, nullptr, stream};
+    return run_gemm(a, 2, 0);
 }
 
 namespace {

@@ -33,23 +33,6 @@ __device__ __forceinline__ float wave_sum(float v)
     return v;
 }
 
-__device__ __forceinline__ void unpack8(const u32x4 &u, float (&f)[8])
-{
-    const bf16x8 b = as_bf16x8(u);
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-        f[i] = static_cast<float>(b[i]);
-}
-
-__device__ __forceinline__ u32x4 pack8f(const float (&f)[8])
-{
-    bf16x8 b;
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-        b[i] = static_cast<__bf16>(f[i]);
-    return __builtin_bit_cast(u32x4, b);
-}
-
 }  // namespace
 
 constexpr int kLnWaves = 4;       // waves (rows in flight) per workgroup
@@ -251,13 +234,12 @@ swiglu_fwd_kernel(const uint16_t *__restrict__ U, const uint16_t *__restrict__ V
         unpack8(*reinterpret_cast<const u32x4 *>(V + t * 8), v);
 #pragma unroll
         for (int i = 0; i < 8; ++i)
-            y[i] = u[i] / (1.0f + __expf(-u[i])) * v[i];
+            y[i] = swiglu(u[i], v[i]);
         *reinterpret_cast<u32x4 *>(Y + t * 8) = pack8f(y);
     }
 }
 
-// Its backward: du = dy v silu'(u), dv = dy silu(u), with
-// silu'(u) = sigma(u) (1 + u (1 - sigma(u))).
+// Its backward.
 __global__ void __launch_bounds__(256)
 swiglu_bwd_kernel(const uint16_t *__restrict__ U, const uint16_t *__restrict__ V,
                   const uint16_t *__restrict__ dY, uint16_t *__restrict__ dU,
@@ -270,11 +252,8 @@ swiglu_bwd_kernel(const uint16_t *__restrict__ U, const uint16_t *__restrict__ V
         unpack8(*reinterpret_cast<const u32x4 *>(V + t * 8), v);
         unpack8(*reinterpret_cast<const u32x4 *>(dY + t * 8), dy);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const float sg = 1.0f / (1.0f + __expf(-u[i]));
-            du[i] = dy[i] * v[i] * sg * (1.0f + u[i] * (1.0f - sg));
-            dv[i] = dy[i] * u[i] * sg;
-        }
+        for (int i = 0; i < 8; ++i)
+            swiglu_grad(u[i], v[i], dy[i], du[i], dv[i]);
         *reinterpret_cast<u32x4 *>(dU + t * 8) = pack8f(du);
         *reinterpret_cast<u32x4 *>(dV + t * 8) = pack8f(dv);
     }

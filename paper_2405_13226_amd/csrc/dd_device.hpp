@@ -61,6 +61,36 @@ __device__ __forceinline__ bf16x4 pack4(float a, float b, float c, float d)
     return r;
 }
 
+// Eight bf16 values of a 16-byte piece as fp32, and back (RNE).
+__device__ __forceinline__ void unpack8(const u32x4 &u, float (&f)[8])
+{
+    const bf16x8 b = as_bf16x8(u);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        f[i] = static_cast<float>(b[i]);
+}
+
+__device__ __forceinline__ u32x4 pack8f(const float (&f)[8])
+{
+    bf16x8 b;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        b[i] = static_cast<__bf16>(f[i]);
+    return __builtin_bit_cast(u32x4, b);
+}
+
+// SwiGLU y = silu(u) v with silu(u) = u / (1 + exp(-u)).
+__device__ __forceinline__ float swiglu(float u, float v) { return u / (1.0f + __expf(-u)) * v; }
+
+// Its gradients: du = dy v silu'(u), dv = dy silu(u), with
+// silu'(u) = sigma(u) (1 + u (1 - sigma(u))).
+__device__ __forceinline__ void swiglu_grad(float u, float v, float dy, float &du, float &dv)
+{
+    const float sg = 1.0f / (1.0f + __expf(-u));
+    du = dy * v * sg * (1.0f + u * (1.0f - sg));
+    dv = dy * u * sg;
+}
+
 // Document span of row-local position p (0 <= p < L) of row b:
 // [ds, de) is the part of p's document inside the row.  Without cu_doclens
 // the whole row is one document.  The result is clamped to contain p, so

@@ -97,37 +97,136 @@ __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c)
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// Eight bf16 values from LDS to C + at, with R's added first if given.
-__device__ __forceinline__ void store_piece(const uint16_t *src, uint16_t *C, const uint16_t *R,
-                                            long long at)
-{
-    u32x4 v = *reinterpret_cast<const u32x4 *>(src);
-    if (R != nullptr) {
-        const bf16x8 x = as_bf16x8(v), y = as_bf16x8(*reinterpret_cast<const u32x4 *>(R + at));
-        bf16x8 z;
-#pragma unroll
-        for (int t = 0; t < 8; ++t)
-            z[t] = static_cast<__bf16>(static_cast<float>(x[t]) + static_cast<float>(y[t]));
-        v = __builtin_bit_cast(u32x4, z);
-    }
-    *reinterpret_cast<u32x4 *>(C + at) = v;
-}
-
 // Row strides (elements) from which a load's per-lane byte offset, up to 7
 // rows, may not fit 32 bits; the loads then take per-lane 64-bit addresses.
 constexpr long long kGemmWideStride = 1LL << 28;
 
-// TA: A is stored [K][M]; TB: B is stored [N][K]; PART: write an fp32
-// partial tile of split blockIdx.y to P ([splits][M][N]) instead of C; WIDE:
-// a row stride of A or B is at least kGemmWideStride.
-// R (optional, not with PART): a bf16 matrix with row stride ldc added to
-// the rounded product before the final rounding (C may be R itself).
-template <bool TA, bool TB, bool PART, bool WIDE>
-__global__ void __launch_bounds__(512, 1)
-gemm_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint16_t *C,
-            float *__restrict__ P, const uint16_t *R, int M, int N, int K, long long lda,
-            long long ldb, long long ldc, int k_len)
+// What becomes of the tile (EPI):
+//   kEpiStore      C = op(A) op(B), plus R (bf16, row stride ldc, may be C
+//                  itself) added to the rounded product before the final
+//                  rounding if given
+//   kEpiPart       an fp32 partial tile of split blockIdx.y to P
+//                  ([splits][groups][M][N])
+//   kEpiSwiglu     half of the tile's columns are A B[0] and half the same
+//                  columns of A B[1]: C[0] and C[1] receive them, C[2]
+//                  silu(C[0]) * C[1] of the rounded values
+//   kEpiSwigluBwd  the rounded tile is the gradient of silu(U) * V: C[0] and
+//                  C[1] receive the gradients of U and V (row stride ldc)
+enum GemmEpi { kEpiStore, kEpiPart, kEpiSwiglu, kEpiSwigluBwd };
+
+// One launch computes, with the same strides,
+//   groups:   C[g] = op(A[0]) op(B[g]), g < groups, or
+//   segments: C[0] = sum over s < segs of op(A[s]) op(B[s])
+// (one of the two counts is 1).
+struct GemmOperands {
+    const uint16_t *A[3], *B[3];
+    uint16_t *C[3];
+    const uint16_t *R, *U, *V;
+    float *P;
+};
+
+// Sizes: M x N per group, K per segment; k_len of a split (segs * K without
+// splits); tiles_n = tile columns of all groups.
+struct GemmSizes {
+    int M, N, K, k_len, tiles_n;
+    long long lda, ldb, ldc;
+};
+
+// LDS position (elements) of the four columns c .. c + 3 of row r of the
+// finished BM x BN bf16 tile.  With kEpiSwiglu the column halves are two
+// tiles of their own.  A row's 4-element group x sits at x ^ (2 (r mod 16))
+// (mod 8 where a row has 16 groups), which keeps the two groups of a 16-byte piece adjacent and spreads one
+// write instruction's 16 rows over the LDS banks.
+template <int BM, int BN, int EPI>
+__device__ __forceinline__ int epi_off(int r, int c)
 {
+    constexpr int W = EPI == kEpiSwiglu ? BN / 2 : BN;
+    return c / W * (BM * W) + r * W + 4 * (((c % W) >> 2) ^ (2 * (r & (W == 64 ? 7 : 15))));
+}
+
+// Writes the finished tile of rows m0 .., columns n0 .. from LDS to memory.
+template <int BM, int BN, int EPI>
+__device__ __forceinline__ void epi_store(const uint16_t *lds, const GemmOperands &op, int grp,
+                                          int m0, int n0, long long ldc, int tid)
+{
+    constexpr int W = EPI == kEpiSwiglu ? BN / 2 : BN, CPR = W / 8;
+    uint16_t *C = op.C[EPI == kEpiStore ? grp : 0];
+#pragma unroll 4
+    for (int it = 0; it < BM * CPR / 512; ++it) {
+        const int idx = it * 512 + tid, r = idx / CPR, c = idx % CPR * 8;
+        const u32x4 v = *reinterpret_cast<const u32x4 *>(lds + epi_off<BM, W, kEpiStore>(r, c));
+        const long long at = (m0 + r) * ldc + n0 + c;
+        if constexpr (EPI == kEpiSwiglu) {
+            const u32x4 w =
+                *reinterpret_cast<const u32x4 *>(lds + BM * W + epi_off<BM, W, kEpiStore>(r, c));
+            float x[8], y[8], z[8];
+            unpack8(v, x);
+            unpack8(w, y);
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                z[t] = swiglu(x[t], y[t]);
+            *reinterpret_cast<u32x4 *>(C + at) = v;
+            *reinterpret_cast<u32x4 *>(op.C[1] + at) = w;
+            *reinterpret_cast<u32x4 *>(op.C[2] + at) = pack8f(z);
+        } else if constexpr (EPI == kEpiSwigluBwd) {
+            float d[8], x[8], y[8], dx[8], dy[8];
+            unpack8(v, d);
+            unpack8(*reinterpret_cast<const u32x4 *>(op.U + at), x);
+            unpack8(*reinterpret_cast<const u32x4 *>(op.V + at), y);
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                swiglu_grad(x[t], y[t], d[t], dx[t], dy[t]);
+            *reinterpret_cast<u32x4 *>(C + at) = pack8f(dx);
+            *reinterpret_cast<u32x4 *>(op.C[1] + at) = pack8f(dy);
+        } else if (op.R != nullptr) {
+            float x[8], y[8];
+            unpack8(v, x);
+            unpack8(*reinterpret_cast<const u32x4 *>(op.R + at), y);
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                x[t] += y[t];
+            *reinterpret_cast<u32x4 *>(C + at) = pack8f(x);
+        } else {
+            *reinterpret_cast<u32x4 *>(C + at) = v;
+        }
+    }
+}
+
+// The pointers of the K steps still to load: moves one step on, or to the
+// next segment's start (all scalar).
+struct GemmWalk {
+    const uint16_t *pa, *pb, *a1, *b1, *a2, *b2;
+    int left, seg_steps;
+
+    __device__ __forceinline__ void init(const GemmOperands &p, int grp, long long oa,
+                                         long long ob, int steps)
+    {
+        pa = p.A[0] + oa;
+        pb = p.B[grp] + ob;
+        a1 = p.A[1] + oa;
+        b1 = p.B[1] + ob;
+        a2 = p.A[2] + oa;
+        b2 = p.B[2] + ob;
+        left = seg_steps = steps;
+    }
+    __device__ __forceinline__ void next(long long ka, long long kb)
+    {
+        const bool sw = --left == 0;
+        pa = sw ? a1 : pa + ka;
+        pb = sw ? b1 : pb + kb;
+        a1 = sw ? a2 : a1;
+        b1 = sw ? b2 : b1;
+        left = sw ? seg_steps : left;
+    }
+};
+
+// TA: A is stored [K][M]; TB: B is stored [N][K]; WIDE: a row stride of A
+// or B is at least kGemmWideStride.
+template <bool TA, bool TB, int EPI, bool WIDE>
+__global__ void __launch_bounds__(512, 1)
+gemm_kernel(GemmOperands op, GemmSizes sz)
+{
+    const long long lda = sz.lda, ldb = sz.ldb, ldc = sz.ldc;
     using T = GemmTile;
     __shared__ __attribute__((aligned(1024))) uint16_t lds[2 * T::SIDE];
 
@@ -135,7 +234,7 @@ gemm_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int l16 = lane & 15, g = lane >> 4;
     const int wm = wave >> 2, wn = wave & 3;
-    const int tiles_n = N / T::BN;
+    const int tiles_n = sz.tiles_n;
     // Workgroups are dispatched round-robin over the 8 XCDs (block id % 8),
     // each with its own L2.  Without a K split, XCD x takes the tile rows x,
     // x + 8, ..., in bands of kGR of its rows; a band is walked in groups of
@@ -143,10 +242,10 @@ gemm_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint
     // per CU of the XCD), so the tiles that run at the same time share kGR
     // A panels and kGC B panels in one L2.
     int tm, tn;
-    if (gridDim.y == 1 && (M / T::BM) % kXcds == 0) {
+    if (gridDim.y == 1 && (sz.M / T::BM) % kXcds == 0) {
         constexpr int kGR = 4, kGC = 8;
         const int x = static_cast<int>(blockIdx.x) % kXcds, k = static_cast<int>(blockIdx.x) / kXcds;
-        const int rows_x = (M / T::BM) / kXcds;
+        const int rows_x = (sz.M / T::BM) / kXcds;
         const int band = k / (kGR * tiles_n), rem = k % (kGR * tiles_n);
         const int gr = min(kGR, rows_x - band * kGR);  // rows of this band
         const int grp_c = rem / (gr * kGC), w = rem % (gr * kGC);
@@ -156,9 +255,11 @@ gemm_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint
         tm = static_cast<int>(blockIdx.x) / tiles_n;
         tn = static_cast<int>(blockIdx.x) % tiles_n;
     }
-    const int m0 = tm * T::BM, n0 = tn * T::BN;
-    const int kbeg = static_cast<int>(blockIdx.y) * k_len;
-    const int nkt = min(k_len, K - kbeg) / T::BK;
+    // Columns of one matrix B[g] (C[g]) in a tile.
+    constexpr int NC = EPI == kEpiSwiglu ? T::BN / 2 : T::BN;
+    const int m0 = tm * T::BM, tpg = sz.N / NC, grp = tn / tpg, n0 = (tn - grp * tpg) * NC;
+    const int kbeg = static_cast<int>(blockIdx.y) * sz.k_len;
+    const int nkt = sz.k_len / T::BK;
 
     // Loads: sub-tile rows of 128 bytes, eight of them per wave instruction
     // (1 KiB); lane i takes row 8 wave + i / 8, stored chunk i % 8.
@@ -166,10 +267,13 @@ gemm_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint
     const int xa = ((lane & 7) ^ (TA ? swz<64>(qrow) : row_swz(qrow))) * 8;
     const int xb = ((lane & 7) ^ (TB ? row_swz(qrow) : swz<64>(qrow))) * 8;
     const long long va = (qr * lda + xa) * 2, vb = (qr * ldb + xb) * 2;  // bytes
-    const uint16_t *pa = A + 8 * wave * lda +
-                         (TA ? static_cast<long long>(kbeg) * lda + m0 : static_cast<long long>(m0) * lda + kbeg);
-    const uint16_t *pb = B + 8 * wave * ldb +
-                         (TB ? static_cast<long long>(n0) * ldb + kbeg : static_cast<long long>(kbeg) * ldb + n0);
+    GemmWalk at;
+    at.init(op, grp,
+            8 * wave * lda + (TA ? static_cast<long long>(kbeg) * lda + m0
+                                 : static_cast<long long>(m0) * lda + kbeg),
+            8 * wave * ldb + (TB ? static_cast<long long>(n0) * ldb + kbeg
+                                 : static_cast<long long>(kbeg) * ldb + n0),
+            sz.K / T::BK);
     // Sub-tile s starts 64 rows (stored along the tile's rows) or 64 columns
     // further; K step kt moves 64 rows or columns.
     const long long sa = TA ? 64 : 64 * lda, sb = TB ? 64 * ldb : 64;
@@ -181,16 +285,20 @@ gemm_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint
         else
             dma_b128_off(p, static_cast<uint32_t>(v), l);
     };
-    // Half h of A (B) of the K step that pa (pb) points at, into stage S.
-    auto load_a = [&](int h, int S, const uint16_t *p) __attribute__((always_inline)) {
+    // From half 0 to half 1 of B: the next 128 columns, or the other matrix.
+    const long long hb = EPI == kEpiSwiglu ? op.B[1] - op.B[0] : 2 * sb;
+    // Half h of A (B) of the next K step to load, into stage S.
+    auto load_a = [&](int h, int S) __attribute__((always_inline)) {
+        const uint16_t *p = at.pa;
         const uint32_t l = lds0 + 2u * (2 * h + S) * T::HALF;
         load(p + 2 * h * sa, va, l);
         load(p + 2 * h * sa + sa, va, l + 2u * T::SUB);
     };
-    auto load_b = [&](int h, int S, const uint16_t *p) __attribute__((always_inline)) {
+    auto load_b = [&](int h, int S) __attribute__((always_inline)) {
+        const uint16_t *p = at.pb + h * hb;
         const uint32_t l = lds0 + 2u * (T::SIDE + (2 * h + S) * T::HALF);
-        load(p + 2 * h * sb, vb, l);
-        load(p + 2 * h * sb + sb, vb, l + 2u * T::SUB);
+        load(p, vb, l);
+        load(p + sb, vb, l + 2u * T::SUB);
     };
 
     // Fragments.  A half h: rows 64 wm + 16 i .. +15 of the half, i.e.
@@ -280,25 +388,24 @@ gemm_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint
         constexpr int S = decltype(stage)::value, MODE = decltype(mode)::value;
         read_b(b0, 0, S);
         if constexpr (MODE == 0)
-            load_a(0, S, pa);
+            load_a(0, S);
         wait_and_barrier<MODE == 0 ? 12 : MODE == 1 ? 10 : 2>();
         products(acc[0][0], a0, b0);
         read_b(b1, 1, S);
         if constexpr (MODE == 0)
-            load_b(0, S, pb);
+            load_b(0, S);
         wait_and_barrier<MODE == 0 ? 12 : MODE == 1 ? 8 : 0>();
         products(acc[0][1], a0, b1);
         read_a(a1, 1, S);
         if constexpr (MODE == 0)
-            load_b(1, S, pb);
+            load_b(1, S);
         wait_and_barrier<MODE == 0 ? 12 : MODE == 1 ? 6 : 0>();
         products(acc[1][1], a1, b1);
         if constexpr (MODE != 2)
             read_a(a0, 0, 1 - S);
         if constexpr (MODE == 0) {
-            load_a(1, S, pa);
-            pa += ka;
-            pb += kb;
+            load_a(1, S);
+            at.next(ka, kb);
         }
         wait_and_barrier<MODE == 0 ? 12 : MODE == 1 ? 4 : 0>();
         products(acc[1][0], a1, b0);
@@ -312,19 +419,17 @@ gemm_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint
             *reinterpret_cast<u32x4 *>(lds + (x >> 2) * T::SIDE + ((x >> 1) & 1) * 2 * T::HALF +
                                        (x & 1) * T::SUB + tid * 8) = u32x4{};
     } else {
-        load_a(0, 0, pa);
-        load_b(0, 0, pb);
-        load_b(1, 0, pb);
-        load_a(1, 0, pa);
-        pa += ka;
-        pb += kb;
+        load_a(0, 0);
+        load_b(0, 0);
+        load_b(1, 0);
+        load_a(1, 0);
+        at.next(ka, kb);
     }
-    load_a(0, 1, pa);
-    load_b(0, 1, pb);
-    load_b(1, 1, pb);
-    load_a(1, 1, pa);
-    pa += ka;
-    pb += kb;
+    load_a(0, 1);
+    load_b(0, 1);
+    load_b(1, 1);
+    load_a(1, 1);
+    at.next(ka, kb);
     wait_and_barrier<8>();
     read_a(a0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
@@ -343,8 +448,9 @@ gemm_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint
 
     // Accumulator (ha, hb, i, j), register e: row m = 128 ha + 64 wm + 16 i +
     // l16, column n = 128 hb + 32 wn + 16 j + 4 g + e of the tile.
-    if constexpr (PART) {
-        float *dst = P + static_cast<long long>(blockIdx.y) * M * N;
+    if constexpr (EPI == kEpiPart) {
+        const int N = sz.N;
+        float *dst = op.P + static_cast<long long>(blockIdx.y * (tiles_n / tpg) + grp) * sz.M * N;
 #pragma unroll
         for (int x = 0; x < 16; ++x) {
             const int ha = x >> 3, i = (x >> 1) & 3, hb = x & 1;
@@ -356,10 +462,7 @@ gemm_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint
         }
     } else {
         // The tile in bf16 through LDS, then to memory in 16-byte pieces of
-        // rows.  The 4-element group n/4 of row r is stored at group
-        // (n/4) ^ (2 (r mod 16)), which keeps the two groups of a 16-byte
-        // piece adjacent and spreads one write instruction's 16 rows over
-        // the LDS banks.
+        // rows.
         __syncthreads();
 #pragma unroll
         for (int x = 0; x < 16; ++x) {
@@ -367,21 +470,14 @@ gemm_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint
             const int r = 128 * ha + 64 * wm + 16 * i + l16;
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                const int n = 128 * hb + 32 * wn + 16 * j + 4 * g;
                 const f32x4 v = acc[ha][hb][i][j];
-                *reinterpret_cast<bf16x4 *>(lds + r * T::BN + 4 * ((n >> 2) ^ (2 * (r & 15)))) =
+                *reinterpret_cast<bf16x4 *>(lds + epi_off<T::BM, T::BN, EPI>(
+                                                      r, 128 * hb + 32 * wn + 16 * j + 4 * g)) =
                     pack4(v[0], v[1], v[2], v[3]);
             }
         }
         __syncthreads();
-#pragma unroll 4
-        for (int it = 0; it < T::BM * T::BN / 8 / (64 * T::NW); ++it) {
-            const int idx = it * 64 * T::NW + tid;
-            const int r = idx >> 5, ch = idx & 31;
-            const uint16_t *src = lds + r * T::BN + 8 * (ch ^ (r & 15));
-            const long long at = (m0 + r) * ldc + n0 + ch * 8;
-            store_piece(src, C, R, at);
-        }
+        epi_store<T::BM, T::BN, EPI>(lds, op, grp, m0, n0, ldc, tid);
     }
 }
 
@@ -406,12 +502,11 @@ struct GemmSmallTile {
     static constexpr int STAGE = 4 * SUB;  // A sub-tiles 0, 1, B sub-tiles 0, 1
 };
 
-template <bool TA, bool TB, bool PART, bool WIDE>
+template <bool TA, bool TB, int EPI, bool WIDE>
 __global__ void __launch_bounds__(512, 1)
-gemm_small_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint16_t *C,
-                  float *__restrict__ P, const uint16_t *R, int M, int N, int K, long long lda,
-                  long long ldb, long long ldc, int k_len)
+gemm_small_kernel(GemmOperands op, GemmSizes sz)
 {
+    const long long lda = sz.lda, ldb = sz.ldb, ldc = sz.ldc;
     using T = GemmSmallTile;
     __shared__ __attribute__((aligned(1024))) uint16_t lds[T::NST * T::STAGE];
 
@@ -420,7 +515,7 @@ gemm_small_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B
     const int l16 = lane & 15, g = lane >> 4;
     const int wm = wave >> 2, wn = wave & 3;
     // Tile rows x, x + 8, ... on XCD x where the rows divide over the XCDs.
-    const int tiles_m = M / T::BM, tiles_n = N / T::BN;
+    const int tiles_m = sz.M / T::BM, tiles_n = sz.tiles_n;
     int tm, tn;
     if (gridDim.y == 1 && tiles_m % kXcds == 0) {
         const int x = static_cast<int>(blockIdx.x) % kXcds, k = static_cast<int>(blockIdx.x) / kXcds;
@@ -431,18 +526,23 @@ gemm_small_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B
         tm = static_cast<int>(blockIdx.x) / tiles_n;
         tn = static_cast<int>(blockIdx.x) % tiles_n;
     }
-    const int m0 = tm * T::BM, n0 = tn * T::BN;
-    const int kbeg = static_cast<int>(blockIdx.y) * k_len;
-    const int nkt = min(k_len, K - kbeg) / T::BK;
+    // Columns of one matrix B[g] (C[g]) in a tile.
+    constexpr int NC = EPI == kEpiSwiglu ? T::BN / 2 : T::BN;
+    const int m0 = tm * T::BM, tpg = sz.N / NC, grp = tn / tpg, n0 = (tn - grp * tpg) * NC;
+    const int kbeg = static_cast<int>(blockIdx.y) * sz.k_len;
+    const int nkt = sz.k_len / T::BK;
 
     const int qr = lane >> 3, qrow = 8 * wave + qr;
     const int xa = ((lane & 7) ^ (TA ? swz<64>(qrow) : row_swz(qrow))) * 8;
     const int xb = ((lane & 7) ^ (TB ? row_swz(qrow) : swz<64>(qrow))) * 8;
     const long long va = (qr * lda + xa) * 2, vb = (qr * ldb + xb) * 2;  // bytes
-    const uint16_t *pa = A + 8 * wave * lda +
-                         (TA ? static_cast<long long>(kbeg) * lda + m0 : static_cast<long long>(m0) * lda + kbeg);
-    const uint16_t *pb = B + 8 * wave * ldb +
-                         (TB ? static_cast<long long>(n0) * ldb + kbeg : static_cast<long long>(kbeg) * ldb + n0);
+    GemmWalk at;
+    at.init(op, grp,
+            8 * wave * lda + (TA ? static_cast<long long>(kbeg) * lda + m0
+                                 : static_cast<long long>(m0) * lda + kbeg),
+            8 * wave * ldb + (TB ? static_cast<long long>(n0) * ldb + kbeg
+                                 : static_cast<long long>(kbeg) * ldb + n0),
+            sz.K / T::BK);
     const long long sa = TA ? 64 : 64 * lda, sb = TB ? 64 * ldb : 64;
     const long long ka = TA ? 64 * lda : 64, kb = TB ? 64 : 64 * ldb;
     const uint32_t lds0 = lds_base_sgpr(lds) + 1024u * wave;
@@ -452,15 +552,16 @@ gemm_small_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B
         else
             dma_b128_off(p, static_cast<uint32_t>(v), l);
     };
-    // The K step that pa and pb point at, into stage st; moves them on.
+    // From sub-tile 0 to sub-tile 1 of B: the next 64 columns, or the other matrix.
+    const long long hb = EPI == kEpiSwiglu ? op.B[1] - op.B[0] : sb;
+    // The next K step to load, into stage st.
     auto load_step = [&](int st) __attribute__((always_inline)) {
         const uint32_t l = lds0 + 2u * T::STAGE * st;
-        load(pa, va, l);
-        load(pb, vb, l + 4u * T::SUB);
-        load(pa + sa, va, l + 2u * T::SUB);
-        load(pb + sb, vb, l + 6u * T::SUB);
-        pa += ka;
-        pb += kb;
+        load(at.pa, va, l);
+        load(at.pb, vb, l + 4u * T::SUB);
+        load(at.pa + sa, va, l + 2u * T::SUB);
+        load(at.pb + hb, vb, l + 6u * T::SUB);
+        at.next(ka, kb);
     };
 
     const int e4 = l16 >> 2, c4 = l16 & 3;
@@ -551,8 +652,9 @@ gemm_small_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B
 
     // Accumulator (i, j), register e: row m = 64 wm + 16 i + l16, column
     // n = 32 wn + 16 j + 4 g + e of the tile; stored as in the large kernel.
-    if constexpr (PART) {
-        float *dst = P + static_cast<long long>(blockIdx.y) * M * N;
+    if constexpr (EPI == kEpiPart) {
+        const int N = sz.N;
+        float *dst = op.P + static_cast<long long>(blockIdx.y * (tiles_n / tpg) + grp) * sz.M * N;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -566,39 +668,37 @@ gemm_small_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B
             const int r = 64 * wm + 16 * i + l16;
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                const int n = 32 * wn + 16 * j + 4 * g;
                 const f32x4 v = acc[i][j];
-                *reinterpret_cast<bf16x4 *>(lds + r * T::BN + 4 * ((n >> 2) ^ (2 * (r & 15)))) =
+                *reinterpret_cast<bf16x4 *>(
+                    lds + epi_off<T::BM, T::BN, EPI>(r, 32 * wn + 16 * j + 4 * g)) =
                     pack4(v[0], v[1], v[2], v[3]);
             }
         }
         __syncthreads();
-#pragma unroll
-        for (int it = 0; it < T::BM * T::BN / 8 / (64 * T::NW); ++it) {
-            const int idx = it * 64 * T::NW + tid;
-            const int r = idx >> 4, ch = idx & 15;
-            store_piece(lds + r * T::BN + 8 * (ch ^ (r & 15)), C, R, (m0 + r) * ldc + n0 + ch * 8);
-        }
+        epi_store<T::BM, T::BN, EPI>(lds, op, grp, m0, n0, ldc, tid);
     }
 }
 
-// C = sum over splits of P (fp32 [splits][M][N]) rounded to bf16; 8 elements
-// per thread, grid-stride.
+// C[g] = sum over splits of P (fp32 [splits][groups][M][N]) rounded to bf16;
+// 8 elements per thread, grid-stride.
 __global__ void __launch_bounds__(256)
-gemm_reduce_kernel(const float *__restrict__ P, uint16_t *C, const uint16_t *R, long long MN,
-                   int splits, long long ldc, int N)
+gemm_reduce_kernel(GemmOperands op, int groups, long long MN, int splits, long long ldc, int N)
 {
+    const float *__restrict__ P = op.P;
+    const uint16_t *R = op.R;
+    const long long all = groups * MN;
     const long long stride = static_cast<long long>(gridDim.x) * 256;
-    for (long long v = static_cast<long long>(blockIdx.x) * 256 + threadIdx.x; v < MN / 8;
+    for (long long v = static_cast<long long>(blockIdx.x) * 256 + threadIdx.x; v < all / 8;
          v += stride) {
         const long long e0 = v * 8;
         f32x4 s0 = *reinterpret_cast<const f32x4 *>(P + e0);
         f32x4 s1 = *reinterpret_cast<const f32x4 *>(P + e0 + 4);
         for (int s = 1; s < splits; ++s) {
-            s0 += *reinterpret_cast<const f32x4 *>(P + s * MN + e0);
-            s1 += *reinterpret_cast<const f32x4 *>(P + s * MN + e0 + 4);
+            s0 += *reinterpret_cast<const f32x4 *>(P + s * all + e0);
+            s1 += *reinterpret_cast<const f32x4 *>(P + s * all + e0 + 4);
         }
-        const long long m = e0 / N, n = e0 % N;
+        const int grp = static_cast<int>(e0 / MN);
+        const long long m = (e0 - grp * MN) / N, n = e0 % N;
         if (R != nullptr) {
             const bf16x8 r = as_bf16x8(*reinterpret_cast<const u32x4 *>(R + m * ldc + n));
 #pragma unroll
@@ -607,28 +707,25 @@ gemm_reduce_kernel(const float *__restrict__ P, uint16_t *C, const uint16_t *R, 
                 s1[t] = static_cast<float>(static_cast<__bf16>(s1[t])) + static_cast<float>(r[t + 4]);
             }
         }
-        *reinterpret_cast<bf16x8 *>(C + m * ldc + n) =
+        *reinterpret_cast<bf16x8 *>(op.C[grp] + m * ldc + n) =
             join(pack4(s0[0], s0[1], s0[2], s0[3]), pack4(s1[0], s1[1], s1[2], s1[3]));
     }
 }
 
-#define DD_GEMM_ARGS                                                                             \
-    const uint16_t *__restrict__, const uint16_t *__restrict__, uint16_t *, float *__restrict__, \
-        const uint16_t *, int, int, int, long long, long long, long long, int
-#define DD_GEMM_INST(TA, TB)                                                                     \
-    template __global__ void gemm_kernel<TA, TB, false, false>(DD_GEMM_ARGS);                    \
-    template __global__ void gemm_kernel<TA, TB, true, false>(DD_GEMM_ARGS);                     \
-    template __global__ void gemm_kernel<TA, TB, false, true>(DD_GEMM_ARGS);                     \
-    template __global__ void gemm_kernel<TA, TB, true, true>(DD_GEMM_ARGS);                      \
-    template __global__ void gemm_small_kernel<TA, TB, false, false>(DD_GEMM_ARGS);              \
-    template __global__ void gemm_small_kernel<TA, TB, true, false>(DD_GEMM_ARGS);               \
-    template __global__ void gemm_small_kernel<TA, TB, false, true>(DD_GEMM_ARGS);               \
-    template __global__ void gemm_small_kernel<TA, TB, true, true>(DD_GEMM_ARGS)
-DD_GEMM_INST(false, false);
-DD_GEMM_INST(false, true);
-DD_GEMM_INST(true, false);
+#define DD_GEMM_INST(TA, TB, EPI)                                                                \
+    template __global__ void gemm_kernel<TA, TB, EPI, false>(GemmOperands, GemmSizes);           \
+    template __global__ void gemm_kernel<TA, TB, EPI, true>(GemmOperands, GemmSizes);            \
+    template __global__ void gemm_small_kernel<TA, TB, EPI, false>(GemmOperands, GemmSizes);     \
+    template __global__ void gemm_small_kernel<TA, TB, EPI, true>(GemmOperands, GemmSizes)
+DD_GEMM_INST(false, false, kEpiStore);
+DD_GEMM_INST(false, false, kEpiPart);
+DD_GEMM_INST(false, true, kEpiStore);
+DD_GEMM_INST(false, true, kEpiPart);
+DD_GEMM_INST(true, false, kEpiStore);
+DD_GEMM_INST(true, false, kEpiPart);
+DD_GEMM_INST(false, false, kEpiSwiglu);
+DD_GEMM_INST(false, true, kEpiSwigluBwd);
 #undef DD_GEMM_INST
-#undef DD_GEMM_ARGS
 
 // Estimated time (us) of a product on tiles of `edge` with `splits` K parts:
 // rounds of workgroups over the CUs (one per CU), each a start-up and tail
@@ -646,10 +743,11 @@ static double gemm_cost(double tiles, double cus, double steps, double splits, d
     return rounds * (std::ceil(steps / splits) * step + (small ? 5.5 : 6.0)) + reduce;
 }
 
-// The cheapest of large or small tiles and 1, 2, 4, ... K splits.  Splits
-// are multiples of 64 and at least 1024 long, and more of them than two
-// large tiles per CU are never needed.
-GemmPlan gemm_plan(int M, int N, int K)
+// The cheapest of large or small tiles and 1, 2, 4, ... K splits for a
+// product of M x N (all groups' columns together) over K.  Splits are
+// multiples of 64 and at least 1024 long, and more of them than two large
+// tiles per CU are never needed.
+GemmPlan gemm_plan(int M, long long N, long long K, bool may_split)
 {
     const int cus = std::max(device_cu_count(), 1);
     const long long tiles = static_cast<long long>(M / GemmTile::BM) * (N / GemmTile::BN);
@@ -664,57 +762,66 @@ GemmPlan gemm_plan(int M, int N, int K)
                 best = GemmPlan{small, s};
             }
         }
-        if (tiles * s >= 2LL * cus || K / (2 * s) < 1024 || (K / (2 * s)) % GemmTile::BK != 0)
+        if (!may_split || tiles * s >= 2LL * cus || K / (2 * s) < 1024 ||
+            (K / (2 * s)) % GemmTile::BK != 0)
             return best;
     }
 }
 
-size_t gemm_workspace_bytes(int M, int N, int K)
+size_t gemm_workspace_bytes(int M, int N, int K, int groups)
 {
-    const GemmPlan p = gemm_plan(M, N, K);
-    return p.splits > 1 ? static_cast<size_t>(p.splits) * M * N * sizeof(float) : 0;
+    const GemmPlan p = gemm_plan(M, static_cast<long long>(groups) * N, K, true);
+    return p.splits > 1 ? static_cast<size_t>(p.splits) * groups * M * N * sizeof(float) : 0;
 }
 
 int launch_gemm(const GemmArgs &a)
 {
     hipStream_t st = static_cast<hipStream_t>(a.stream);
-    const GemmPlan plan = gemm_plan(a.M, a.N, a.K);
+    // Columns of all groups (of both matrices for kEpiSwiglu).
+    const bool swiglu = a.kind == GemmArgs::kSwiglu;
+    const long long cols = static_cast<long long>(swiglu ? 2 : a.groups) * a.N;
+    const GemmPlan plan = gemm_plan(a.M, cols, static_cast<long long>(a.segs) * a.K,
+                                    a.kind == GemmArgs::kPlain && a.segs == 1);
     const int splits = plan.splits;
-    const int k_len = a.K / splits;
     const int edge = plan.small ? GemmSmallTile::BM : GemmTile::BM;
-    const dim3 grid(static_cast<unsigned>((a.M / edge) * (a.N / edge)),
-                    static_cast<unsigned>(splits));
-    const uint16_t *A = static_cast<const uint16_t *>(a.A);
-    const uint16_t *B = static_cast<const uint16_t *>(a.B);
-    uint16_t *C = static_cast<uint16_t *>(a.C);
-    float *P = static_cast<float *>(a.workspace);
-    const uint16_t *R = static_cast<const uint16_t *>(a.R);
-    const bool part = splits > 1;
+    GemmOperands op{};
+    for (int i = 0; i < 3; ++i) {
+        op.A[i] = static_cast<const uint16_t *>(a.A[i]);
+        op.B[i] = static_cast<const uint16_t *>(a.B[i]);
+        op.C[i] = static_cast<uint16_t *>(a.C[i]);
+    }
+    op.R = static_cast<const uint16_t *>(a.R);
+    op.U = static_cast<const uint16_t *>(a.U);
+    op.V = static_cast<const uint16_t *>(a.V);
+    op.P = static_cast<float *>(a.workspace);
+    const int tiles_n = static_cast<int>(cols / edge);
+    const GemmSizes sz{a.M, a.N, a.K, a.K / splits * a.segs, tiles_n, a.lda, a.ldb, a.ldc};
+    const dim3 grid(static_cast<unsigned>(a.M / edge) * tiles_n, static_cast<unsigned>(splits));
     const bool wide = a.lda >= kGemmWideStride || a.ldb >= kGemmWideStride;
-    auto pick = [&](auto ta, auto tb) {
+    auto pick = [&](auto ta, auto tb, auto epi) {
         constexpr bool TA = decltype(ta)::value, TB = decltype(tb)::value;
-        if (plan.small) {
-            if (wide)
-                return part ? gemm_small_kernel<TA, TB, true, true>
-                            : gemm_small_kernel<TA, TB, false, true>;
-            return part ? gemm_small_kernel<TA, TB, true, false>
-                        : gemm_small_kernel<TA, TB, false, false>;
-        }
-        if (wide)
-            return part ? gemm_kernel<TA, TB, true, true> : gemm_kernel<TA, TB, false, true>;
-        return part ? gemm_kernel<TA, TB, true, false> : gemm_kernel<TA, TB, false, false>;
+        constexpr int E = decltype(epi)::value;
+        if (plan.small)
+            return wide ? gemm_small_kernel<TA, TB, E, true> : gemm_small_kernel<TA, TB, E, false>;
+        return wide ? gemm_kernel<TA, TB, E, true> : gemm_kernel<TA, TB, E, false>;
     };
-    const auto kern = a.trans_a   ? pick(IC<1>{}, IC<0>{})
-                      : a.trans_b ? pick(IC<0>{}, IC<1>{})
-                                  : pick(IC<0>{}, IC<0>{});
-    hipError_t e = launch_kernel(kern, grid, dim3(512), st, A, B, C, P, R, a.M, a.N, a.K, a.lda,
-                                 a.ldb, a.ldc, k_len);
-    if (e != hipSuccess || !part)
+    auto form = [&](auto epi) {
+        return a.trans_a   ? pick(IC<1>{}, IC<0>{}, epi)
+               : a.trans_b ? pick(IC<0>{}, IC<1>{}, epi)
+                           : pick(IC<0>{}, IC<0>{}, epi);
+    };
+    const auto kern = swiglu                                ? pick(IC<0>{}, IC<0>{}, IC<kEpiSwiglu>{})
+                      : a.kind == GemmArgs::kSwigluBackward ? pick(IC<0>{}, IC<1>{}, IC<kEpiSwigluBwd>{})
+                      : splits > 1                          ? form(IC<kEpiPart>{})
+                                                            : form(IC<kEpiStore>{});
+    hipError_t e = launch_kernel(kern, grid, dim3(512), st, op, sz);
+    if (e != hipSuccess || splits == 1)
         return e == hipSuccess ? DD_OK : DD_ERR_HIP;
     const long long MN = static_cast<long long>(a.M) * a.N;
-    const unsigned blocks = static_cast<unsigned>(std::min<long long>((MN / 8 + 255) / 256, 8192));
-    e = launch_kernel(gemm_reduce_kernel, dim3(blocks), dim3(256), st,
-                      static_cast<const float *>(P), C, R, MN, splits, a.ldc, a.N);
+    const unsigned blocks =
+        static_cast<unsigned>(std::min<long long>((a.groups * MN / 8 + 255) / 256, 8192));
+    e = launch_kernel(gemm_reduce_kernel, dim3(blocks), dim3(256), st, op, a.groups, MN, splits,
+                      a.ldc, a.N);
     return e == hipSuccess ? DD_OK : DD_ERR_HIP;
 }
 

@@ -64,15 +64,23 @@ constexpr size_t kNoAllocScratchBytes = static_cast<size_t>(16) << 20;
 // device with the device current).  Returns DD_OK or DD_ERR_HIP.
 int noalloc_scratch(void **ptr);
 
-// C[M, N] = op(A) op(B) (dd_gemm.hip); M and N multiples of 256, K of 64.
+// Products of dd_gemm.hip, M and N multiples of 256, K of 64:
+//   kPlain           C[g] = op(A[0]) op(B[g]) (+ R), g < groups, or, with
+//                    segs > 1, C[0] = sum over s < segs of op(A[s]) op(B[s])
+//   kSwiglu          C[0] = A[0] B[0], C[1] = A[0] B[1], C[2] = silu(C[0]) C[1]
+//   kSwigluBackward  C[0], C[1] = gradients of silu(U) V for the upstream
+//                    gradient A[0] B[0]^T
 struct GemmArgs {
-    const void *A, *B;
-    void *C;
+    enum Kind { kPlain, kSwiglu, kSwigluBackward } kind;
+    const void *A[3], *B[3];
+    void *C[3];
     const void *R;            // optional residual added to C (bf16, row stride ldc)
+    const void *U, *V;        // kSwigluBackward inputs (row stride ldc)
     long long lda, ldb, ldc;  // row strides in elements
-    int M, N, K;
+    int groups, segs;         // at most 3, one of them 1
+    int M, N, K;              // per group and segment
     bool trans_a, trans_b;    // A stored [K][M]; B stored [N][K] (not both)
-    void *workspace;          // fp32 [splits][M][N] of gemm_plan, if it splits
+    void *workspace;          // fp32 [splits][groups][M][N] of gemm_plan, if it splits
     void *stream;
 };
 // How a product of these sizes runs: on 256 x 256 or (small) 128 x 128 tiles,
@@ -81,8 +89,8 @@ struct GemmPlan {
     bool small;
     int splits;
 };
-GemmPlan gemm_plan(int M, int N, int K);
-size_t gemm_workspace_bytes(int M, int N, int K);
+GemmPlan gemm_plan(int M, long long N, long long K, bool may_split);
+size_t gemm_workspace_bytes(int M, int N, int K, int groups);
 int launch_gemm(const GemmArgs &a);
 
 // LayerNorm over rows of d elements (dd_block.hip), d in {512, 1024, 2048}.

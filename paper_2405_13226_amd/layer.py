@@ -12,12 +12,10 @@ embeddings):
 
 LayerNorms have weight and bias, projections have none, the SwiGLU width is
 5632 at d = 2048.  Every step runs in this library's HIP kernels: the
-projections and the MLP products in its bf16 GEMM (the residual additions in
-the GEMM epilogue; the forward multiplies by transposed copies of the weights,
-made by its transpose kernel at the start of the step, so that both operands
-of every forward product are read along rows, the GEMM's faster form), the
-LayerNorms and the SwiGLU in its elementwise kernels,
-RoPE and attention in the attention kernels; the backward is written out
+projections and the MLP products in its bf16 GEMM (the residual additions
+and the SwiGLU, forward and backward, in the GEMM epilogue; products that
+share an input or are summed run as one launch), the LayerNorms in their own
+kernels, RoPE and attention in the attention kernels; the backward is written out
 step by step (one autograd node for the whole block).  The block exists to
 place the attention hot path in a full layer step: its time as a share of
 the step, and the step time's growth with the sequence length at a fixed
@@ -43,20 +41,15 @@ class _BlockFunction(torch.autograd.Function):
                 docs, doc_pos):
         B, L, H, D = shape
         d = H * D
-        # transposed weight copies: every forward product then reads both of
-        # its operands along rows (the GEMM's faster operand form)
-        t_qkv, t_o, t_1, t_3, t_2 = (ops.transpose(w) for w in (w_qkv, w_o, w_1, w_3, w_2))
         a, mean1, rstd1 = ops.layer_norm(x, ln1_w, ln1_b, LN_EPS)
-        q, k, v = (ops.gemm(a, t_qkv[i * d:(i + 1) * d], trans_b=True) for i in range(3))
+        q, k, v = ops.gemm_group(a, [w_qkv[:, i * d:(i + 1) * d] for i in range(3)])
         o, lse, qr, kr = forward_rope(q.view(B, L, H, D), k.view(B, L, H, D),
                                       v.view(B, L, H, D), base, True, docs, doc_pos)
         o2 = o.view(B * L, d)
-        h = ops.gemm(o2, t_o, trans_b=True, residual=x)
+        h = ops.gemm(o2, w_o, residual=x)
         m, mean2, rstd2 = ops.layer_norm(h, ln2_w, ln2_b, LN_EPS)
-        u1, u3 = ops.gemm(m, t_1, trans_b=True), ops.gemm(m, t_3, trans_b=True)
-        g = ops.swiglu(u1, u3)
-        y = ops.gemm(g, t_2, trans_b=True, residual=h)
-        del t_qkv, t_o, t_1, t_3, t_2
+        u1, u3, g = ops.gemm_swiglu(m, w_1, w_3)
+        y = ops.gemm(g, w_2, residual=h)
         ctx.save_for_backward(x, ln1_w, w_qkv, w_o, ln2_w, w_1, w_3, w_2, a, mean1, rstd1, qr,
                               kr, v, o, lse, h, m, mean2, rstd2, u1, u3, g)
         ctx.cfg = (shape, base, docs, doc_pos)
@@ -70,13 +63,10 @@ class _BlockFunction(torch.autograd.Function):
         d = H * D
         dy = dy.contiguous()
         # MLP: y = h + swiglu(m W1, m W3) W2
-        dg = ops.gemm(dy, w_2, trans_b=True)
+        du1, du3 = ops.gemm_swiglu_backward(dy, w_2, u1, u3)
         dw_2 = ops.gemm(g, dy, trans_a=True)
-        du1, du3 = ops.swiglu_backward(u1, u3, dg)
-        dm = ops.gemm(du1, w_1, trans_b=True)
-        ops.gemm(du3, w_3, trans_b=True, residual=dm, out=dm)
-        dw_1 = ops.gemm(m, du1, trans_a=True)
-        dw_3 = ops.gemm(m, du3, trans_a=True)
+        dm = ops.gemm_sum([du1, du3], [w_1, w_3], trans_b=True)
+        dw_1, dw_3 = ops.gemm_group(m, [du1, du3], trans_a=True)
         dh, dln2_w, dln2_b = ops.layer_norm_backward(h, ln2_w, mean2, rstd2, dm, dres=dy)
         # attention: h = x + attn(RoPE(q), RoPE(k), v) Wo
         do = ops.gemm(dh, w_o, trans_b=True)
@@ -84,12 +74,10 @@ class _BlockFunction(torch.autograd.Function):
         dq, dk, dv = backward_rope(qr, kr, v.view(B, L, H, D), o, lse, do.view(B, L, H, D),
                                    base, True, docs, doc_pos)
         grads = [t.view(B * L, d) for t in (dq, dk, dv)]
-        da = ops.gemm(grads[0], w_qkv[:, :d], trans_b=True)
-        for i in (1, 2):
-            ops.gemm(grads[i], w_qkv[:, i * d:(i + 1) * d], trans_b=True, residual=da, out=da)
+        columns = [slice(i * d, (i + 1) * d) for i in range(3)]
+        da = ops.gemm_sum(grads, [w_qkv[:, c] for c in columns], trans_b=True)
         dw_qkv = torch.empty_like(w_qkv)
-        for i in range(3):
-            ops.gemm(a, grads[i], trans_a=True, out=dw_qkv[:, i * d:(i + 1) * d])
+        ops.gemm_group(a, grads, trans_a=True, outs=[dw_qkv[:, c] for c in columns])
         dx, dln1_w, dln1_b = ops.layer_norm_backward(x, ln1_w, mean1, rstd1, da, dres=dh)
         return (dx, dln1_w, dln1_b, dw_qkv, dw_o, dln2_w, dln2_b, dw_1, dw_3, dw_2,
                 None, None, None, None)

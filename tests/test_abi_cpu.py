@@ -223,6 +223,32 @@ def test_block_kernel_validation(lib):
     assert gemm(C=fake(0, 1024)) == ALIAS           # C overlaps A
     assert gemm(R=fake(2, 64)) == ALIAS             # R partly overlaps C
     assert lib.dd_gemm_workspace_bytes(255, 256, 64) == 0
+    # Joint products: counts, shapes, aliasing between column-slice outputs
+    def arr(*p):
+        return (ctypes.c_void_p * len(p))(*p)
+    def group(n=2, B=(fake(1), fake(2)), C=(fake(3), fake(4)), M=256, N=256, K=64, ldc=256):
+        return lib.dd_gemm_group(fake(0), K, 0, arr(*B), N, 0, arr(*C), ldc, n, M, N, K, None, 0,
+                                 None)
+    assert group(n=0) == SHAPE and group(n=4) == SHAPE and group(N=300) == SHAPE
+    assert group(B=(fake(1), None)) == NULL and group(C=(None, fake(4))) == NULL
+    assert group(C=(fake(3), fake(1, 64))) == ALIAS       # an output over an operand
+    assert group(C=(fake(3), fake(3, 256)), ldc=512) == ALIAS  # columns 0.. and 128..
+    assert group(C=(fake(3), fake(3, 768)), ldc=512) == ALIAS  # columns 0.. and 384.. (wraps)
+    assert group(C=(fake(3), fake(3, 8))) == ALIGN
+    total = lambda A, n=2, K=64: lib.dd_gemm_sum(arr(*A), K, arr(fake(1), fake(2)), 256, 0,
+                                                 fake(3), 256, n, 256, 256, K, None)
+    assert total((fake(0), None)) == NULL and total((fake(0), fake(4)), n=4) == SHAPE
+    assert total((fake(0), fake(4)), K=96) == SHAPE
+    assert total((fake(0), fake(3, 16))) == ALIAS
+    assert lib.dd_gemm_swiglu(fake(0), 64, fake(1), None, 256, fake(3), fake(4), fake(5), 256,
+                              256, 256, 64, None) == NULL
+    assert lib.dd_gemm_swiglu(fake(0), 64, fake(1), fake(2), 256, fake(3), fake(4), fake(3), 256,
+                              256, 256, 64, None) == ALIAS
+    assert lib.dd_gemm_swiglu_bwd(fake(0), 64, fake(1), 64, None, fake(2), fake(3), fake(4), 256,
+                                  256, 256, 64, None) == NULL
+    assert lib.dd_gemm_swiglu_bwd(fake(0), 64, fake(1), 64, fake(2), fake(5), fake(2), fake(4),
+                                  256, 256, 256, 64, None) == ALIAS
+    assert lib.dd_gemm_group_workspace_bytes(256, 256, 64, 4) == 0
     # LayerNorm
     ln = lambda **kw: lib.dd_layernorm_fwd(kw.get("X", fake(0)), fake(1), fake(2),
                                            kw.get("Y", fake(3)), fake(4), fake(5),

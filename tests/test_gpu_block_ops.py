@@ -109,6 +109,52 @@ def test_gemm_strided_slices_and_residual(cuda):
     assert rel_l2(f64(acc), ref2) <= RTOL2
 
 
+# Small tiles, and large ones (one and more per CU, ragged over the XCDs).
+JOINT = [(256, 256, 64), (512, 768, 192), (2304, 2816, 128), (4096, 4096, 192)]
+
+
+@pytest.mark.parametrize("n", [2, 3])
+@pytest.mark.parametrize("M,N,K", JOINT + [(512, 512, 8192)])  # the last splits K
+def test_gemm_group(cuda, M, N, K, n):
+    # both uses: columns of one weight matrix, and weight gradients written
+    # into columns of one matrix
+    a, w = bf16((M, K), 1).to(cuda), bf16((K, n * N), 2).to(cuda)
+    cols = [slice(i * N, (i + 1) * N) for i in range(n)]
+    for c, got in zip(cols, ops.gemm_group(a, [w[:, c] for c in cols])):
+        assert rel_l2(f64(got), f64(a) @ f64(w[:, c])) <= RTOL
+    x, ys = bf16((K, M), 3).to(cuda), [bf16((K, N), 4 + i).to(cuda) for i in range(n)]
+    out = torch.zeros((M, n * N + 256), dtype=torch.bfloat16, device=cuda)
+    ops.gemm_group(x, ys, trans_a=True, outs=[out[:, c] for c in cols])
+    for c, y in zip(cols, ys):
+        assert rel_l2(f64(out[:, c]), f64(x).T @ f64(y)) <= RTOL
+    assert not out[:, n * N:].any()
+
+
+@pytest.mark.parametrize("n", [1, 2, 3])
+@pytest.mark.parametrize("M,N,K", JOINT)
+def test_gemm_sum(cuda, M, N, K, n):
+    xs = [bf16((M, K), 1 + i).to(cuda) for i in range(n)]
+    w = bf16((N, n * K), 9).to(cuda)
+    ws = [w[:, i * K:(i + 1) * K] for i in range(n)]
+    got = ops.gemm_sum(xs, ws, trans_b=True)
+    assert rel_l2(f64(got), sum(f64(x) @ f64(v).T for x, v in zip(xs, ws))) <= RTOL
+    got = ops.gemm_sum(xs, [v.t().contiguous() for v in ws])
+    assert rel_l2(f64(got), sum(f64(x) @ f64(v).T for x, v in zip(xs, ws))) <= RTOL
+
+
+@pytest.mark.parametrize("M,N,K", JOINT)
+def test_gemm_swiglu_is_the_products_and_the_swiglu(cuda, M, N, K):
+    # bit for bit the separate launches: same sums, same roundings
+    x, w1, w3 = bf16((M, K), 1).to(cuda), bf16((K, N), 2, 0.1).to(cuda), bf16((K, N), 3, 0.1).to(cuda)
+    u, v, y = ops.gemm_swiglu(x, w1, w3)
+    assert torch.equal(u, ops.gemm(x, w1)) and torch.equal(v, ops.gemm(x, w3))
+    assert torch.equal(y, ops.swiglu(u, v))
+    dy, w2 = bf16((M, K), 4).to(cuda), bf16((N, K), 5, 0.1).to(cuda)
+    du, dv = ops.gemm_swiglu_backward(dy, w2, u, v)
+    ru, rv = ops.swiglu_backward(u, v, ops.gemm(dy, w2, trans_b=True))
+    assert torch.equal(du, ru) and torch.equal(dv, rv)
+
+
 def ln_ref(x, w, b, dy, dres, eps=1e-5):
     mu = x.mean(1, keepdims=True)
     var = ((x - mu) ** 2).mean(1, keepdims=True)
