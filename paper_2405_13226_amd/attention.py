@@ -20,14 +20,19 @@ from ._lib import check, lib
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 def _stream(dev):
-    return ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
+    # the current stream's handle without a Stream object (a small call's
+    # host time is a few dozen microseconds, of which the object is three)
+    return torch._C._cuda_getCurrentRawStream(dev.index)
 
 
 def _check_tensor(t, name, shape=None, dtype=torch.bfloat16):
+    if (isinstance(t, torch.Tensor) and t.dtype is dtype and t.is_cuda and t.is_contiguous()
+            and (shape is None or t.shape == shape)):
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.device.type != "cuda":

@@ -14,19 +14,15 @@ import ctypes
 import torch
 
 from ._lib import check, lib
+from .attention import _ptr as _p, _stream
 
 LN_EPS = 1e-5
 
 
-def _p(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
-
-
-def _stream(dev):
-    return ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
-
-
 def _mat(t, name):
+    if (isinstance(t, torch.Tensor) and t.dim() == 2 and t.is_cuda
+            and t.dtype is torch.bfloat16 and t.stride(1) == 1):
+        return
     if not isinstance(t, torch.Tensor) or t.dim() != 2:
         raise ValueError(f"{name} must be a 2-D tensor")
     if t.device.type != "cuda" or t.dtype != torch.bfloat16:
