@@ -36,7 +36,15 @@ __device__ __forceinline__ float wave_sum(float v)
 }  // namespace
 
 constexpr int kLnWaves = 4;       // waves (rows in flight) per workgroup
-constexpr int kLnRowsPerWg = 64;  // rows per workgroup in the backward
+
+// Rows per workgroup of the backward: few enough that every CU has four
+// workgroups (a row is a chain of loads, two reductions and a store: 2048
+// rows of 1024 took 26.5 us at 64 rows, 6.7 at 8), but each has 8 or
+// more, since every workgroup writes a row of column partials.
+__host__ __device__ constexpr int ln_rows_per_wg(int rows)
+{
+    return rows >= 65536 ? 64 : rows <= 8192 ? 8 : (rows + 4095) / 4096 * 4;
+}
 
 // CH = d / 512 chunks of 8 elements per lane.
 template <int CH>
@@ -88,7 +96,7 @@ layernorm_fwd_kernel(const uint16_t *__restrict__ X, const uint16_t *__restrict_
     }
 }
 
-// Backward over kLnRowsPerWg rows per workgroup (each wave takes every
+// Backward over ln_rows_per_wg rows per workgroup (each wave takes every
 // kLnWaves-th row); partial column sums of dy * xhat and dy go to
 // part[blockIdx.x][0..d) and part[blockIdx.x][d..2d).
 template <int CH>
@@ -109,8 +117,9 @@ layernorm_bwd_kernel(const uint16_t *__restrict__ X, const uint16_t *__restrict_
         for (int i = 0; i < 8; ++i)
             dw[c][i] = db[c][i] = 0.f;
     }
-    const int row0 = static_cast<int>(blockIdx.x) * kLnRowsPerWg;
-    for (int rr = wave; rr < kLnRowsPerWg; rr += kLnWaves) {
+    const int per_wg = ln_rows_per_wg(rows);
+    const int row0 = static_cast<int>(blockIdx.x) * per_wg;
+    for (int rr = wave; rr < per_wg; rr += kLnWaves) {
         const int row = row0 + rr;
         if (row >= rows)
             break;
@@ -278,7 +287,9 @@ template __global__ void layernorm_bwd_kernel<4>(DD_LNB_ARGS);
 size_t layernorm_workspace_bytes(int rows, int d)
 {
     // The workgroups' partial rows, then the chunk sums.
-    const long long nparts = (rows + kLnRowsPerWg - 1) / kLnRowsPerWg;
+    // (At most 1024 of them below 65,536 rows; the bound grows with the rows,
+    // so that scratch for the longest input serves every shorter one.)
+    const long long nparts = rows >= 65536 ? (rows + 63LL) / 64 : std::min((rows + 7) / 8, 1024);
     return static_cast<size_t>(nparts + kLnChunks) * 2 * d * sizeof(float);
 }
 
@@ -302,7 +313,7 @@ int launch_layernorm_fwd(const LayerNormArgs &a)
 int launch_layernorm_bwd(const LayerNormArgs &a)
 {
     hipStream_t st = static_cast<hipStream_t>(a.stream);
-    const int nparts = (a.rows + kLnRowsPerWg - 1) / kLnRowsPerWg;
+    const int per_wg = ln_rows_per_wg(a.rows), nparts = (a.rows + per_wg - 1) / per_wg;
     const dim3 grid(static_cast<unsigned>(nparts)), block(64 * kLnWaves);
     const auto *X = static_cast<const uint16_t *>(a.X);
     const auto *W = static_cast<const uint16_t *>(a.w);
