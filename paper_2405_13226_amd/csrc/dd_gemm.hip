@@ -482,38 +482,48 @@ gemm_kernel(GemmOperands op, GemmSizes sz)
 }
 
 // ---------------------------------------------------------------------------
-// The 128 x 128 tile, for products whose 256 x 256 tiles would leave CUs
-// idle.  Eight waves, wave (wm, wn) owning rows 64 wm .. +63 and columns
-// 32 wn .. +31: one phase of 16 products per K step.  With one workgroup per
-// CU nothing else hides a load's latency, so four stages (128 KiB) hold the
-// step being read and three in flight (three or five measured the same or
-// slower); the two groups of four waves run half a phase apart as in the
-// large kernel.
+// Smaller tiles, for products whose 256 x 256 tiles would leave CUs idle:
+// 128 x 128 (SmallTile) and 256 x 128 (TallTile).  Eight waves in two groups
+// that run half a phase apart, as in the large kernel; a phase is 16 products
+// of every wave: one K step of the small tile (a wave owns 64 x 32), half of
+// one (32 k) of the tall tile (64 x 64).  With one workgroup per CU nothing
+// else hides a load's latency, so further stages beside the one being read
+// are in flight: three of four for the small tile (128 KiB; two or four more
+// measured the same or slower), two of three for the tall one (144 KiB).
 //
-// What bounds the loop: the LDS.  A step reads 96 KiB and receives 32 KiB,
-// 1024 clocks at 128 bytes each; it takes 0.41 us (0.86 us of products per
-// 256 x 256 step, a quarter of that here).  Reading 64 KiB instead (each
-// group of four waves taking half of the step's k for the whole tile, the
-// two sums added at the end) measured 6% faster at K = 5632 and 5% slower at
-// K = 1024.  2048 x 1024 x 1024: 21.1 us on 32 large tiles, 11.4-12.6 here.
-struct GemmSmallTile {
-    static constexpr int BM = 128, BN = 128, BK = 64, NW = 8, NST = 4;
-    static constexpr int SUB = 64 * 64;
-    static constexpr int STAGE = 4 * SUB;  // A sub-tiles 0, 1, B sub-tiles 0, 1
+// What bounds the loop: the LDS, 128 bytes per clock.  A step of the small
+// tile reads 96 KiB and receives 32 (1024 clocks; 0.41 us measured), of the
+// tall one 128 and 48 (1408 clocks; 0.60), of the large one 192 and 64
+// (2048 clocks, its products' time).  Letting each group take half of the
+// k for the whole small tile reads 64 KiB a step and measured 6% faster at
+// K = 5632, 5% slower at K = 1024 (the sums have to be added at the end).
+// 2048 x 1024 x 1024: 21.1 us on 32 large tiles, 11.4-12.6 on small ones.
+struct SmallTile {
+    static constexpr int BM = 128, BN = 128, BK = 64, NST = 4;
+    static constexpr int PH = 1;  // phases per K step
+};
+struct TallTile {
+    static constexpr int BM = 256, BN = 128, BK = 64, NST = 3;
+    static constexpr int PH = 2;
 };
 
-template <bool TA, bool TB, int EPI, bool WIDE>
+template <typename T, bool TA, bool TB, int EPI, bool WIDE>
 __global__ void __launch_bounds__(512, 1)
-gemm_small_kernel(GemmOperands op, GemmSizes sz)
+gemm_mid_kernel(GemmOperands op, GemmSizes sz)
 {
     const long long lda = sz.lda, ldb = sz.ldb, ldc = sz.ldc;
-    using T = GemmSmallTile;
-    __shared__ __attribute__((aligned(1024))) uint16_t lds[T::NST * T::STAGE];
+    constexpr int SUB = 64 * 64;
+    constexpr int NA = T::BM / 64, NB = T::BN / 64;   // sub-tiles of A, of B
+    constexpr int STAGE = (NA + NB) * SUB;
+    constexpr int LPS = NA + NB;                      // a wave's loads per step
+    constexpr int WN = T::BM == 256 ? 2 : 4;          // waves along N
+    constexpr int NJ = T::BN / WN / 16;               // 16-column blocks per wave
+    __shared__ __attribute__((aligned(1024))) uint16_t lds[T::NST * STAGE];
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int l16 = lane & 15, g = lane >> 4;
-    const int wm = wave >> 2, wn = wave & 3;
+    const int wm = wave / WN, wn = wave % WN, group = wave >> 2;
     // Tile rows x, x + 8, ... on XCD x where the rows divide over the XCDs.
     const int tiles_m = sz.M / T::BM, tiles_n = sz.tiles_n;
     int tm, tn;
@@ -546,28 +556,25 @@ gemm_small_kernel(GemmOperands op, GemmSizes sz)
     const long long sa = TA ? 64 : 64 * lda, sb = TB ? 64 * ldb : 64;
     const long long ka = TA ? 64 * lda : 64, kb = TB ? 64 : 64 * ldb;
     const uint32_t lds0 = lds_base_sgpr(lds) + 1024u * wave;
-    auto load = [&](const uint16_t *p, long long v, uint32_t l) __attribute__((always_inline)) {
+    // From sub-tile 0 to sub-tile 1 of B: the next 64 columns, or the other matrix.
+    const long long hb = EPI == kEpiSwiglu ? op.B[1] - op.B[0] : sb;
+    // Load i of the next K step to load, into stage st: the A sub-tiles, then
+    // the B sub-tiles.
+    auto load = [&](int i, int st) __attribute__((always_inline)) {
+        const uint32_t l = lds0 + 2u * (STAGE * st + i * SUB);
+        const uint16_t *p = i < NA ? at.pa + i * sa : at.pb + (i - NA) * hb;
+        const long long v = i < NA ? va : vb;
         if constexpr (WIDE)
             dma_b128(reinterpret_cast<const char *>(p) + v, l);
         else
             dma_b128_off(p, static_cast<uint32_t>(v), l);
     };
-    // From sub-tile 0 to sub-tile 1 of B: the next 64 columns, or the other matrix.
-    const long long hb = EPI == kEpiSwiglu ? op.B[1] - op.B[0] : sb;
-    // The next K step to load, into stage st.
-    auto load_step = [&](int st) __attribute__((always_inline)) {
-        const uint32_t l = lds0 + 2u * T::STAGE * st;
-        load(at.pa, va, l);
-        load(at.pb, vb, l + 4u * T::SUB);
-        load(at.pa + sa, va, l + 2u * T::SUB);
-        load(at.pb + hb, vb, l + 6u * T::SUB);
-        at.next(ka, kb);
-    };
 
     const int e4 = l16 >> 2, c4 = l16 & 3;
-    int fa[TA ? 8 : 2], fb[TB ? 2 : 4];  // element offsets in a stage
+    int fa[TA ? 8 : 2], fb[TB ? 2 : 2 * NJ];  // element offsets in a stage
     {
-        const int as = wm * T::SUB, bs = (2 + (wn >> 1)) * T::SUB;
+        // The wave's first column inside its B sub-tile.
+        const int as = wm * SUB, bs = (NA + wn * 16 * NJ / 64) * SUB, bc = wn * 16 * NJ % 64;
         if constexpr (TA) {
 #pragma unroll
             for (int i = 0; i < 8; ++i)
@@ -580,97 +587,119 @@ gemm_small_kernel(GemmOperands op, GemmSizes sz)
         if constexpr (TB) {
 #pragma unroll
             for (int kk = 0; kk < 2; ++kk)
-                fb[kk] = bs + 64 * (32 * (wn & 1) + l16) + (((4 * kk + g) ^ row_swz(l16)) << 3);
+                fb[kk] = bs + 64 * (bc + l16) + (((4 * kk + g) ^ row_swz(l16)) << 3);
         } else {
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                fb[j] = bs + tile_off<64>(8 * g + 4 * (j & 1) + e4,
-                                          32 * (wn & 1) + 16 * (j >> 1) + 4 * c4);
+            for (int j = 0; j < 2 * NJ; ++j)
+                fb[j] = bs + tile_off<64>(8 * g + 4 * (j & 1) + e4, bc + 16 * (j >> 1) + 4 * c4);
         }
     }
-    f32x4 acc[4][2];
+    f32x4 acc[4][NJ];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < NJ; ++j)
             acc[i][j] = f32x4{};
 
     const int first = min(nkt, T::NST - 1);
-    for (int kt = 0; kt < first; ++kt)
-        load_step(kt);
-    if (nkt > 2)
-        wait_and_barrier<8>();
+    for (int kt = 0; kt < first; ++kt) {
+#pragma unroll
+        for (int i = 0; i < LPS; ++i)
+            load(i, kt);
+        at.next(ka, kb);
+    }
+    if (nkt > T::NST - 2)
+        wait_and_barrier<LPS *(T::NST - 2)>();
     else
         wait_and_barrier<0>();
-    if (wm == 1)
+    if (group == 1)
         plain_barrier();
+    int rs = 0, ws = T::NST - 1;  // the stages read and refilled by a step
     for (int kt = 0; kt < nkt; ++kt) {
-        const uint16_t *st = lds + (kt % T::NST) * T::STAGE;
-        bf16x8 a[4][2], b[2][2];
+        const uint16_t *st = lds + rs * STAGE;
+        constexpr int KK = 2 / T::PH;  // 32-wide parts of the step in a phase
 #pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
+        for (int ph = 0; ph < T::PH; ++ph) {
+            bf16x8 a[4][KK], b[NJ][KK];
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                if constexpr (TB)
-                    b[j][kk] = lds_row8(st + fb[kk] + 1024 * j);
-                else
-                    b[j][kk] = join(lds_tr4(st + fb[2 * j] + 2048 * kk),
-                                    lds_tr4(st + fb[2 * j + 1] + 2048 * kk));
+            for (int x = 0; x < KK; ++x) {
+                const int kk = ph * KK + x;
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    if constexpr (TB)
+                        b[j][x] = lds_row8(st + fb[kk] + 1024 * j);
+                    else
+                        b[j][x] = join(lds_tr4(st + fb[2 * j] + 2048 * kk),
+                                       lds_tr4(st + fb[2 * j + 1] + 2048 * kk));
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if constexpr (TA)
+                        a[i][x] = join(lds_tr4(st + fa[2 * i] + 2048 * kk),
+                                       lds_tr4(st + fa[2 * i + 1] + 2048 * kk));
+                    else
+                        a[i][x] = lds_row8(st + fa[kk] + 1024 * i);
+                }
             }
+            // The stage that the step before has read is refilled; before the
+            // next step starts, its own loads have to be there (the steps
+            // after it may be in flight).
+            const int ahead = nkt - 1 - kt;  // steps after this one
+            if (ahead >= T::NST - 1) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if constexpr (TA)
-                    a[i][kk] = join(lds_tr4(st + fa[2 * i] + 2048 * kk),
-                                    lds_tr4(st + fa[2 * i + 1] + 2048 * kk));
-                else
-                    a[i][kk] = lds_row8(st + fa[kk] + 1024 * i);
+                for (int i = ph * LPS / T::PH; i < (ph + 1) * LPS / T::PH; ++i)
+                    load(i, ws);
             }
+            if (ph + 1 < T::PH) {
+                wait_and_barrier<63>();
+            } else {
+                if (ahead >= T::NST - 1) {
+                    at.next(ka, kb);
+                    wait_and_barrier<LPS *(T::NST - 2)>();
+                } else if (T::NST == 4 && ahead == 2) {
+                    wait_and_barrier<LPS>();
+                } else {
+                    wait_and_barrier<0>();
+                }
+                ws = rs;
+                rs = rs + 1 == T::NST ? 0 : rs + 1;
+            }
+            __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+            for (int x = 0; x < KK; ++x)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j)
+                        acc[i][j] = mfma16(b[j][x], a[i][x], acc[i][j]);  // rows n, columns m
+            __builtin_amdgcn_s_setprio(0);
+            plain_barrier();
         }
-        // The stage that the step before has read takes the step three ahead;
-        // the next step has to be there (the two after it may be in flight).
-        if (kt + 3 < nkt) {
-            load_step((kt + 3) % T::NST);
-            wait_and_barrier<8>();
-        } else if (kt + 2 < nkt) {
-            wait_and_barrier<4>();
-        } else {
-            wait_and_barrier<0>();
-        }
-        __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = mfma16(b[j][kk], a[i][kk], acc[i][j]);  // rows n, columns m
-        __builtin_amdgcn_s_setprio(0);
-        plain_barrier();
     }
-    if (wm == 0)
+    if (group == 0)
         plain_barrier();
 
     // Accumulator (i, j), register e: row m = 64 wm + 16 i + l16, column
-    // n = 32 wn + 16 j + 4 g + e of the tile; stored as in the large kernel.
+    // n = 16 NJ wn + 16 j + 4 g + e of the tile; stored as in the large kernel.
     if constexpr (EPI == kEpiPart) {
         const int N = sz.N;
         float *dst = op.P + static_cast<long long>(blockIdx.y * (tiles_n / tpg) + grp) * sz.M * N;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+            for (int j = 0; j < NJ; ++j)
                 *reinterpret_cast<f32x4 *>(dst + static_cast<long long>(m0 + 64 * wm + 16 * i + l16) * N +
-                                           n0 + 32 * wn + 16 * j + 4 * g) = acc[i][j];
+                                           n0 + 16 * NJ * wn + 16 * j + 4 * g) = acc[i][j];
     } else {
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int r = 64 * wm + 16 * i + l16;
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
+            for (int j = 0; j < NJ; ++j) {
                 const f32x4 v = acc[i][j];
                 *reinterpret_cast<bf16x4 *>(
-                    lds + epi_off<T::BM, T::BN, EPI>(r, 32 * wn + 16 * j + 4 * g)) =
+                    lds + epi_off<T::BM, T::BN, EPI>(r, 16 * NJ * wn + 16 * j + 4 * g)) =
                     pack4(v[0], v[1], v[2], v[3]);
             }
         }
@@ -715,8 +744,14 @@ gemm_reduce_kernel(GemmOperands op, int groups, long long MN, int splits, long l
 #define DD_GEMM_INST(TA, TB, EPI)                                                                \
     template __global__ void gemm_kernel<TA, TB, EPI, false>(GemmOperands, GemmSizes);           \
     template __global__ void gemm_kernel<TA, TB, EPI, true>(GemmOperands, GemmSizes);            \
-    template __global__ void gemm_small_kernel<TA, TB, EPI, false>(GemmOperands, GemmSizes);     \
-    template __global__ void gemm_small_kernel<TA, TB, EPI, true>(GemmOperands, GemmSizes)
+    template __global__ void gemm_mid_kernel<TallTile, TA, TB, EPI, false>(GemmOperands,         \
+                                                                           GemmSizes);           \
+    template __global__ void gemm_mid_kernel<TallTile, TA, TB, EPI, true>(GemmOperands,          \
+                                                                          GemmSizes);            \
+    template __global__ void gemm_mid_kernel<SmallTile, TA, TB, EPI, false>(GemmOperands,        \
+                                                                            GemmSizes);          \
+    template __global__ void gemm_mid_kernel<SmallTile, TA, TB, EPI, true>(GemmOperands,         \
+                                                                           GemmSizes)
 DD_GEMM_INST(false, false, kEpiStore);
 DD_GEMM_INST(false, false, kEpiPart);
 DD_GEMM_INST(false, true, kEpiStore);
@@ -727,39 +762,43 @@ DD_GEMM_INST(false, false, kEpiSwiglu);
 DD_GEMM_INST(false, true, kEpiSwigluBwd);
 #undef DD_GEMM_INST
 
-// Estimated time (us) of a product on tiles of `edge` with `splits` K parts:
-// rounds of workgroups over the CUs (one per CU), each a start-up and tail
-// plus its K steps, then the partial sums' write and read.  The constants
-// are fits to graph-replayed products: 2048 x 1024 at K = 1024 / 2816 / 5632
-// takes 21 / 46 / 85 us on large tiles and 12.6 / 26 / 42 on small ones;
-// with two splits 28 / 38 / 57 and 17 / 26 / 40; a chip full of large tiles
-// runs slower (1.4 us a step) for its power.
+// Estimated time (us) of `tiles` tiles with `splits` K parts: rounds of
+// workgroups over the CUs (one per CU), each a start-up and tail plus its K
+// steps, then the partial sums' write and read.  The constants are fits to
+// graph-replayed products.  One round of large, tall and small tiles: 2048 x
+// 1024 at K = 1024 takes 21 / 15-17 / 12.5-13 us, at K = 5632 88 / 58 / 42-47
+// (with two splits 59 / 44 / 40); 2048 x 2816 at K = 1024 (88, 176 and 352
+// workgroups) 23 / 17 / 23.  A full chip runs slower, large tiles for their
+// power: 8192 x 2048 at K = 2048 (256, 512, 1024 workgroups) 54 / 69 / 86.
 static double gemm_cost(double tiles, double cus, double steps, double splits, double mn,
-                        bool small)
+                        int tile)
 {
     const double wgs = tiles * splits, rounds = std::ceil(wgs / cus);
-    const double step = small ? 0.42 : wgs < cus ? 1.02 + 0.2 * wgs / cus : 1.4;
+    const double part = std::min(wgs / cus, 1.0);  // CUs in use
+    const double step = tile == GemmPlan::kSmall  ? (part < 1 ? 0.42 : 0.55)
+                        : tile == GemmPlan::kTall ? (part < 1 ? 0.60 + 0.15 * part : 0.95)
+                                                  : (part < 1 ? 1.02 + 0.2 * part : 1.4);
     const double reduce = splits > 1 ? 6.0 + splits * mn * 8.0 / 4.0e6 : 0.0;
-    return rounds * (std::ceil(steps / splits) * step + (small ? 5.5 : 6.0)) + reduce;
+    return rounds * (std::ceil(steps / splits) * step + 6.0) + reduce;
 }
 
-// The cheapest of large or small tiles and 1, 2, 4, ... K splits for a
-// product of M x N (all groups' columns together) over K.  Splits are
-// multiples of 64 and at least 1024 long, and more of them than two large
-// tiles per CU are never needed.
+// The cheapest tile and number of K splits (1, 2, 4, ...) for a product of
+// M x N (all groups' columns together) over K.  Splits are multiples of 64
+// and at least 1024 long, and more of them than two large tiles per CU are
+// never needed.
 GemmPlan gemm_plan(int M, long long N, long long K, bool may_split)
 {
     const int cus = std::max(device_cu_count(), 1);
     const long long tiles = static_cast<long long>(M / GemmTile::BM) * (N / GemmTile::BN);
-    GemmPlan best{false, 1};
+    GemmPlan best{GemmPlan::kLarge, 1};
     double cost = -1;
     for (int s = 1;; s *= 2) {
-        for (const bool small : {false, true}) {
-            const double c = gemm_cost(static_cast<double>(small ? 4 * tiles : tiles), cus,
-                                       K / 64.0, s, static_cast<double>(M) * N, small);
+        for (const GemmPlan::Tile tile : {GemmPlan::kLarge, GemmPlan::kTall, GemmPlan::kSmall}) {
+            const double c = gemm_cost(static_cast<double>(tiles << tile), cus, K / 64.0, s,
+                                       static_cast<double>(M) * N, tile);
             if (cost < 0 || c < cost) {
                 cost = c;
-                best = GemmPlan{small, s};
+                best = GemmPlan{tile, s};
             }
         }
         if (!may_split || tiles * s >= 2LL * cus || K / (2 * s) < 1024 ||
@@ -783,7 +822,8 @@ int launch_gemm(const GemmArgs &a)
     const GemmPlan plan = gemm_plan(a.M, cols, static_cast<long long>(a.segs) * a.K,
                                     a.kind == GemmArgs::kPlain && a.segs == 1);
     const int splits = plan.splits;
-    const int edge = plan.small ? GemmSmallTile::BM : GemmTile::BM;
+    const int bm = plan.tile == GemmPlan::kSmall ? SmallTile::BM : GemmTile::BM;
+    const int bn = plan.tile == GemmPlan::kLarge ? GemmTile::BN : SmallTile::BN;
     GemmOperands op{};
     for (int i = 0; i < 3; ++i) {
         op.A[i] = static_cast<const uint16_t *>(a.A[i]);
@@ -794,15 +834,19 @@ int launch_gemm(const GemmArgs &a)
     op.U = static_cast<const uint16_t *>(a.U);
     op.V = static_cast<const uint16_t *>(a.V);
     op.P = static_cast<float *>(a.workspace);
-    const int tiles_n = static_cast<int>(cols / edge);
+    const int tiles_n = static_cast<int>(cols / bn);
     const GemmSizes sz{a.M, a.N, a.K, a.K / splits * a.segs, tiles_n, a.lda, a.ldb, a.ldc};
-    const dim3 grid(static_cast<unsigned>(a.M / edge) * tiles_n, static_cast<unsigned>(splits));
+    const dim3 grid(static_cast<unsigned>(a.M / bm) * tiles_n, static_cast<unsigned>(splits));
     const bool wide = a.lda >= kGemmWideStride || a.ldb >= kGemmWideStride;
     auto pick = [&](auto ta, auto tb, auto epi) {
         constexpr bool TA = decltype(ta)::value, TB = decltype(tb)::value;
         constexpr int E = decltype(epi)::value;
-        if (plan.small)
-            return wide ? gemm_small_kernel<TA, TB, E, true> : gemm_small_kernel<TA, TB, E, false>;
+        if (plan.tile == GemmPlan::kSmall)
+            return wide ? gemm_mid_kernel<SmallTile, TA, TB, E, true>
+                        : gemm_mid_kernel<SmallTile, TA, TB, E, false>;
+        if (plan.tile == GemmPlan::kTall)
+            return wide ? gemm_mid_kernel<TallTile, TA, TB, E, true>
+                        : gemm_mid_kernel<TallTile, TA, TB, E, false>;
         return wide ? gemm_kernel<TA, TB, E, true> : gemm_kernel<TA, TB, E, false>;
     };
     auto form = [&](auto epi) {

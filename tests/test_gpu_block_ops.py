@@ -60,7 +60,8 @@ def test_gemm(cuda, M, N, K, ta, tb):
 
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
 @pytest.mark.parametrize("K", [64, 128, 192, 256, 320])
-@pytest.mark.parametrize("M,N", [(256, 512), (2048, 8192)])  # small tiles; one large tile per CU
+# small tiles; tall tiles (more of them than CUs' halves); one large tile per CU
+@pytest.mark.parametrize("M,N", [(256, 512), (2048, 2816), (2048, 8192)])
 def test_gemm_short_reductions(cuda, M, N, K, ta, tb):
     # 1 to 5 K steps: the pipelined loops' first, last and odd steps
     a = bf16((K, M) if ta else (M, K), K + 1)
@@ -109,8 +110,8 @@ def test_gemm_strided_slices_and_residual(cuda):
     assert rel_l2(f64(acc), ref2) <= RTOL2
 
 
-# Small tiles, and large ones (one and more per CU, ragged over the XCDs).
-JOINT = [(256, 256, 64), (512, 768, 192), (2304, 2816, 128), (4096, 4096, 192)]
+# Small, tall and large tiles (one and more per CU, rows ragged over the XCDs).
+JOINT = [(256, 256, 64), (512, 768, 192), (2304, 2816, 128), (2048, 1536, 320), (4096, 4096, 192)]
 
 
 @pytest.mark.parametrize("n", [2, 3])
