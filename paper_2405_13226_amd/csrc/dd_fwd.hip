@@ -90,11 +90,16 @@ __device__ __forceinline__ FwdItem fwd_item(int bid, int nqb, int B, int L, int 
 // fragments right after loading them (positions and frequencies as
 // dd_rope, so the result is bit-identical to a dd_rope pass) and, when
 // Qrot is not null, writes the rotated rows there for the backward.
+// KS > 1 (not persistent): KS groups of four waves share the block's key
+// tiles, group i taking tiles i, i + KS, ..., each with LDS stages of its
+// own; at the end the groups' sums are put on a common maximum and added
+// through LDS.  For grids of so few blocks that the heaviest one's chain of
+// key tiles is the launch's time (fwd_key_groups).
 // Waves per SIMD: four in the one-block D = 64 form (at most 128 VGPRs),
 // three in the persistent one (its LDS holds three workgroups per CU), two
 // at D = 128.
-template <int D, bool PERSIST, bool ROPE>
-__global__ void __launch_bounds__(256, D == 64 ? (PERSIST ? 3 : 4) : 2)
+template <int D, bool PERSIST, bool ROPE, int KS>
+__global__ void __launch_bounds__(256 * KS, D == 64 ? (PERSIST ? 3 : 4) : 2)
 fwd_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
            const uint16_t *__restrict__ V, uint16_t *__restrict__ O, float *__restrict__ LSE,
            int B, int L, int H, int causal_i, const int32_t *__restrict__ cu, int n_docs,
@@ -107,11 +112,13 @@ fwd_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
     // loads during the current item's last tile (the register budget of
     // three waves per SIMD has no room for a second set of Q fragments).
     constexpr bool kQStage = PERSIST && D == 64;
-    __shared__ __attribute__((aligned(1024))) uint16_t lds[2 * T::STAGE + (kQStage ? T::BM * D : 0)];
+    __shared__ __attribute__((aligned(1024))) uint16_t lds_all[KS * 2 * T::STAGE + (kQStage ? T::BM * D : 0)];
 
     const bool causal = causal_i != 0;
     const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
+    const int group = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8);
+    const int wave = (tid >> 6) & 3, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
+    uint16_t *const lds = lds_all + group * 2 * T::STAGE;
     const long long rs = static_cast<long long>(H) * D;  // token stride
     const int n_items = nqb * B * H;
     const int G = static_cast<int>(gridDim.x);
@@ -182,7 +189,7 @@ fwd_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
                     qf8[kk][2 * e + 1] = static_cast<__bf16>(x1);
                 }
             }
-            if (Qrot != nullptr && q_raw < L) {
+            if (Qrot != nullptr && q_raw < L && group == 0) {
                 uint16_t *dst = Qrot + x.base + q * rs + g * 8;
 #pragma unroll
                 for (int kk = 0; kk < KK; ++kk)
@@ -350,8 +357,10 @@ fwd_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
     setup(it);
     load_q(it, false);
     reset();
-    int t = it.t_begin;
-    issue(it, t, lds);
+    int t = it.t_begin + group;
+    // (with KS = 2, a group's tile past the last is neither loaded nor used)
+    if (KS == 1 || t <= it.t_end)
+        issue(it, t, lds);
     wait_vmem();
     __syncthreads();
 
@@ -360,10 +369,11 @@ fwd_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
     auto step = [&](auto bufc) __attribute__((always_inline)) -> bool {
         constexpr int BUF = decltype(bufc)::value;
         uint16_t *other = lds + (1 - BUF) * T::STAGE;
-        const bool last = t == it.t_end;
+        const bool last = t - group + KS > it.t_end;
         bool more = false;
         if (!last) {
-            issue(it, t + 1, other);
+            if (KS == 1 || t + KS <= it.t_end)
+                issue(it, t + KS, other);
         } else if constexpr (PERSIST) {
             const int nbid = item_bid(k_item + 1, static_cast<int>(blockIdx.x), G, n_items);
             more = nbid >= 0;
@@ -378,7 +388,8 @@ fwd_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
                 }
             }
         }
-        compute(t, bufc);
+        if (KS == 1 || t <= it.t_end)
+            compute(t, bufc);
         if (!kQStage && more)  // Q of the next item (registers free after the tile)
             load_q(nit, false);
         wait_vmem();
@@ -391,7 +402,7 @@ fwd_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
             __syncthreads();
         }
         if (!last) {
-            ++t;
+            t += KS;
             return true;
         }
         if constexpr (!PERSIST) {
@@ -414,6 +425,44 @@ fwd_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
         if (!step(IC<1>{}))
             break;
     }
+    if constexpr (KS > 1) {
+        // The other groups' maxima, sums and accumulators go through LDS (all
+        // tiles have been read); a group that saw no key has m = -inf, l = 0.
+        constexpr int SLOT = 256 * 4;  // floats of one 16-byte piece per lane
+        constexpr int NS = 1 + 4 * DB;
+        float *x = reinterpret_cast<float *>(lds_all) + (tid & 255) * 4;
+        if (group > 0) {
+            float *y = x + (group - 1) * NS * SLOT;
+            *reinterpret_cast<f32x4 *>(y) = f32x4{m_i, l_i, 0.f, 0.f};
+#pragma unroll
+            for (int r = 0; r < 4 * DB; ++r) {
+                f32x4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    v[e] = acc[r >> 2][4 * (r & 3) + e];
+                *reinterpret_cast<f32x4 *>(y + (r + 1) * SLOT) = v;
+            }
+        }
+        __syncthreads();
+        if (group > 0)
+            return;
+#pragma unroll
+        for (int o = 0; o < KS - 1; ++o) {
+            const float *y = x + o * NS * SLOT;
+            const f32x4 ml = *reinterpret_cast<const f32x4 *>(y);
+            const float m = fmaxf(m_i, ml[0]), ref = m == -INFINITY ? 0.f : m;
+            const float a0 = fast_exp2(m_i - ref), a1 = fast_exp2(ml[0] - ref);
+            m_i = m;
+            l_i = l_i * a0 + ml[1] * a1;
+#pragma unroll
+            for (int r = 0; r < 4 * DB; ++r) {
+                const f32x4 v = *reinterpret_cast<const f32x4 *>(y + (r + 1) * SLOT);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    acc[r >> 2][4 * (r & 3) + e] = acc[r >> 2][4 * (r & 3) + e] * a0 + v[e] * a1;
+            }
+        }
+    }
     if constexpr (!PERSIST)
         store();
 }
@@ -425,15 +474,46 @@ fwd_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
     const uint16_t *__restrict__, const uint16_t *__restrict__, const uint16_t *__restrict__,   \
         uint16_t *__restrict__, float *__restrict__, int, int, int, int,                          \
         const int32_t *__restrict__, int, float, int, uint16_t *__restrict__, RopeEpi, int
-template __global__ void fwd_kernel<64, false, false>(DD_FWD_ARGS);
-template __global__ void fwd_kernel<64, true, false>(DD_FWD_ARGS);
-template __global__ void fwd_kernel<128, false, false>(DD_FWD_ARGS);
-template __global__ void fwd_kernel<128, true, false>(DD_FWD_ARGS);
-template __global__ void fwd_kernel<64, false, true>(DD_FWD_ARGS);
-template __global__ void fwd_kernel<64, true, true>(DD_FWD_ARGS);
-template __global__ void fwd_kernel<128, false, true>(DD_FWD_ARGS);
-template __global__ void fwd_kernel<128, true, true>(DD_FWD_ARGS);
+template __global__ void fwd_kernel<64, false, false, 1>(DD_FWD_ARGS);
+template __global__ void fwd_kernel<64, true, false, 1>(DD_FWD_ARGS);
+template __global__ void fwd_kernel<128, false, false, 1>(DD_FWD_ARGS);
+template __global__ void fwd_kernel<128, true, false, 1>(DD_FWD_ARGS);
+template __global__ void fwd_kernel<64, false, true, 1>(DD_FWD_ARGS);
+template __global__ void fwd_kernel<64, true, true, 1>(DD_FWD_ARGS);
+template __global__ void fwd_kernel<128, false, true, 1>(DD_FWD_ARGS);
+template __global__ void fwd_kernel<128, true, true, 1>(DD_FWD_ARGS);
+template __global__ void fwd_kernel<64, false, false, 2>(DD_FWD_ARGS);
+template __global__ void fwd_kernel<128, false, false, 2>(DD_FWD_ARGS);
+template __global__ void fwd_kernel<64, false, true, 2>(DD_FWD_ARGS);
+template __global__ void fwd_kernel<64, false, false, 4>(DD_FWD_ARGS);
+template __global__ void fwd_kernel<64, false, true, 4>(DD_FWD_ARGS);
+template __global__ void fwd_kernel<128, false, true, 2>(DD_FWD_ARGS);
 #undef DD_FWD_ARGS
+
+// Groups of waves over which a query block's keys are split.  All of a small
+// grid's workgroups are resident at once (four per CU at D = 64, two at 128),
+// so nothing balances the causal blocks: the heaviest, with L / 64 key tiles,
+// is the launch's time, and the groups shorten it.  A larger grid is balanced
+// by dispatch, and the groups only cost it their final sum (and at D = 128,
+// where two groups fill a CU, its second workgroup).  Measured, causal, us
+// with 1 / 2 / 4 groups; D = 64: 64 blocks of L = 2048 32 / 24 / 22, 256 of
+// L = 8192 114 / 81 / 70, 256 of L = 512 12.7 / 10.9 / 11.9, 512 of L = 8192
+// 118 / 97 / 90, 480 of L = 300 13.1 / 13.3 / 19.8, 1024 of L = 4096 134 / 103
+// / 106, 1280 of L = 5000 175 / 152 / 158, 768 of L = 1024 34.9 / 35.8 / 42.7,
+// 1536 of L = 8192 255 / 257 / 266.  D = 128: 128 of L = 4096 80 / 62, 512 of
+// L = 4096 117 / 89, 640 of L = 2500 88.5 / 86.2, 1024 of L = 8192 278 / 290,
+// 256 of L = 256 12.4 / 12.7, 384 of L = 1024 35.8 / 35.3, 512 of L = 1024
+// 37 / 42, 512 of L = 2048 65.2 / 66.0.
+template <int D>
+static int fwd_key_groups(long long blocks, int L)
+{
+    const long long cus = device_cu_count();
+    if (D == 64)
+        return blocks <= cus && L > 768                          ? 4
+               : blocks <= 2 * cus || (L > 1024 && blocks <= 5 * cus) ? 2
+                                                                      : 1;
+    return blocks <= cus || (L > 2048 && 2 * blocks <= 5 * cus) ? 2 : 1;
+}
 
 template <int D, bool ROPE>
 static int launch_fwd_d(const FwdArgs &a)
@@ -446,12 +526,18 @@ static int launch_fwd_d(const FwdArgs &a)
     const RopeEpi rt = ROPE ? rope_epi(a.rope_base, D) : RopeEpi{};
     // Persistent for short rows: as many workgroups as are resident at once.
     const long long pgrid =
-        a.L <= kFwdPersistMaxSpan<D> ? persistent_grid<fwd_kernel<D, true, ROPE>>(256) : 0;
+        a.L <= kFwdPersistMaxSpan<D> ? persistent_grid<fwd_kernel<D, true, ROPE, 1>>(256) : 0;
     const bool persist = pgrid > 0 && pgrid < all;
+    const int ks = fwd_key_groups<D>(static_cast<long long>(nqb) * a.B * a.H, a.L);
+    auto kern = persist ? fwd_kernel<D, true, ROPE, 1> : fwd_kernel<D, false, ROPE, 1>;
+    if (ks == 2)
+        kern = fwd_kernel<D, false, ROPE, 2>;
+    if constexpr (D == 64)
+        if (ks == 4)
+            kern = fwd_kernel<D, false, ROPE, 4>;
     ProfScope prof(K_FWD, static_cast<hipStream_t>(a.stream));
     const hipError_t e = launch_kernel(
-        persist ? fwd_kernel<D, true, ROPE> : fwd_kernel<D, false, ROPE>,
-        dim3(static_cast<unsigned>(persist ? pgrid : all)), dim3(256),
+        kern, dim3(static_cast<unsigned>(persist && ks == 1 ? pgrid : all)), dim3(256 * ks),
         static_cast<hipStream_t>(a.stream), a.Q, a.K, a.V, a.O, a.LSE, a.B, a.L, a.H,
         a.causal ? 1 : 0, a.cu, a.n_docs, scale_log2, nqb, a.Qrot, rt, rope);
     return e == hipSuccess ? DD_OK : DD_ERR_HIP;

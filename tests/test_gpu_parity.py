@@ -39,6 +39,19 @@ def test_document_masked_chunks(cuda, D, causal):
     check_case(B, L, H, D, causal=causal, cu=cu, seed=D + causal)
 
 
+# Small grids split a block's tiles over groups of waves (two, or four in the
+# D = 64 forward from L = 769 on): tile counts that the groups do not divide,
+# blocks with fewer tiles than groups, groups whose keys are all masked.
+@pytest.mark.parametrize("L,D", [(768, 64), (769, 64), (1153, 64), (641, 128), (2177, 128)])
+@pytest.mark.parametrize("mode", ["causal", "full", "docs"])
+def test_small_grids_split_over_wave_groups(cuda, L, D, mode):
+    cu = None
+    if mode == "docs":
+        cu = dd.chunk_doclens([L // 3, 1, 70, L - L // 3 - 71], L)
+    check_case(1, L, 2, D, causal=mode != "full", cu=cu, seed=900 + L,
+               tag=f"wave groups L={L} D={D} {mode}")
+
+
 # Short rows take the persistent forms of the forward, dK/dV and (D = 64) dQ
 # kernels, where a workgroup walks several blocks back to back.  Grids:
 # forward 768 (D = 64) / 512 (D = 128) workgroups, dK/dV 512 / 256, dQ 512
