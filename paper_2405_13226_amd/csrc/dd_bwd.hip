@@ -34,6 +34,40 @@
 
 namespace dd {
 
+// Adds the accumulators of wave groups 1 .. KS-1 (256 threads each) to group
+// 0's through LDS at `lds` (16-byte aligned, 16 * DB KiB per further group, all
+// of the workgroup's tiles read).  Returns true for group 0, whose wave i's
+// lanes own the same rows as every other group's wave i.
+template <int KS, int DB>
+__device__ __forceinline__ bool add_group_sums(uint16_t *lds, int group, int tid, f32x16 (&acc)[DB])
+{
+    float *x = reinterpret_cast<float *>(lds) + (tid & 255) * 4;
+    if (group > 0) {
+        float *y = x + (group - 1) * 4 * DB * 1024;
+#pragma unroll
+        for (int r = 0; r < 4 * DB; ++r) {
+            f32x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                v[e] = acc[r >> 2][4 * (r & 3) + e];
+            *reinterpret_cast<f32x4 *>(y + r * 1024) = v;
+        }
+    }
+    __syncthreads();
+    if (group > 0)
+        return false;
+#pragma unroll
+    for (int o = 0; o < KS - 1; ++o)
+#pragma unroll
+        for (int r = 0; r < 4 * DB; ++r) {
+            const f32x4 v = *reinterpret_cast<const f32x4 *>(x + (o * 4 * DB + r) * 1024);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                acc[r >> 2][4 * (r & 3) + e] += v[e];
+        }
+    return true;
+}
+
 // ---------------------------------------------------------------------------
 // 1. dK, dV
 // ---------------------------------------------------------------------------
@@ -57,8 +91,11 @@ struct KvTile1 {
     static constexpr int STAGE = 2 * TILE + 2 * BM * 2;
 };
 
-template <int D, bool PERSIST>
-__global__ void __launch_bounds__(256, 2)
+// KS = 2 (not persistent): eight waves, of which group 1 (waves 4-7) takes
+// every other query tile of the same 128 keys, with LDS stages of its own;
+// its dK and dV are added through LDS at the end (dkdv_query_groups).
+template <int D, bool PERSIST, int KS>
+__global__ void __launch_bounds__(256 * KS, 2)
 dkdv1_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
              const uint16_t *__restrict__ V, const uint16_t *__restrict__ dO,
              const float *__restrict__ lse2g, const float *__restrict__ ndeltag,
@@ -69,11 +106,13 @@ dkdv1_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
     using T = KvTile1<D>;
     constexpr int KK = D / 16;
     constexpr int DB = D / 32;
-    __shared__ __attribute__((aligned(1024))) uint16_t lds[2 * T::STAGE];
+    __shared__ __attribute__((aligned(1024))) uint16_t lds_all[KS * 2 * T::STAGE];
 
     const bool causal = causal_i != 0;
     const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
+    const int group = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8);
+    const int wave = (tid >> 6) & 3, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
+    uint16_t *const lds = lds_all + group * 2 * T::STAGE;
     const long long rs = static_cast<long long>(H) * D;
     const int n_items = nkb * B * H;
     const int G = static_cast<int>(gridDim.x);
@@ -239,8 +278,10 @@ dkdv1_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
         dk[db] = f32x16{};
         dv[db] = f32x16{};
     }
-    int t = it.t_begin;
-    kv_issue<D, T>(plan, lds, Q, dO, lse2g, ndeltag, it, t, L, rs, wave, lane);
+    int t = it.t_begin + group;
+    // (with KS = 2, a group's tile past the last is neither loaded nor used)
+    if (KS == 1 || t <= it.t_end)
+        kv_issue<D, T>(plan, lds, Q, dO, lse2g, ndeltag, it, t, L, rs, wave, lane);
     wait_vmem();
     __syncthreads();
 
@@ -249,10 +290,11 @@ dkdv1_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
     auto step = [&](auto bufc) __attribute__((always_inline)) -> bool {
         constexpr int BUF = decltype(bufc)::value;
         uint16_t *other = lds + (1 - BUF) * T::STAGE;
-        const bool last = t == it.t_end;
+        const bool last = t - group + KS > it.t_end;
         bool more = false;
         if (!last) {
-            kv_issue<D, T>(plan, other, Q, dO, lse2g, ndeltag, it, t + 1, L, rs, wave, lane);
+            if (KS == 1 || t + KS <= it.t_end)
+                kv_issue<D, T>(plan, other, Q, dO, lse2g, ndeltag, it, t + KS, L, rs, wave, lane);
         } else if constexpr (PERSIST) {
             const int nbid = item_bid(k_item + 1, static_cast<int>(blockIdx.x), G, n_items);
             more = nbid >= 0;
@@ -262,14 +304,21 @@ dkdv1_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
                                lane);
             }
         }
-        compute(t, bufc);
+        if (KS == 1 || t <= it.t_end)
+            compute(t, bufc);
         if (more)  // K and V of the next item (registers free after the tile)
             load_kv(nit);
         wait_vmem();
         __syncthreads();
         if (!last) {
-            ++t;
+            t += KS;
             return true;
+        }
+        if constexpr (KS > 1) {
+            const bool own = add_group_sums<KS, DB>(lds_all, group, tid, dk);
+            add_group_sums<KS, DB>(lds_all + KS * T::STAGE, group, tid, dv);
+            if (!own)
+                return false;
         }
         store();
         if (!PERSIST || !more)
@@ -341,10 +390,13 @@ __device__ __forceinline__ QItem q_item(int bid, int nqb, int B, int L, int H, b
 // it DMAs the next block's first K/V tile into the free stage and the next
 // block's Q and dO rows into LDS areas of their own (read into registers
 // after that tile), and loads its O rows and LSE into registers.
+// KS > 1 (not persistent): KS groups of four waves share the block's key
+// tiles, group i taking tiles i, i + KS, ..., each with LDS stages of its
+// own; the groups' dQ are added through LDS at the end (dq_key_groups).
 // Waves per SIMD: four in the one-block D = 64 form (at most 128 VGPRs),
 // two otherwise (the persistent form's item loop and D = 128 need more).
-template <int D, bool PERSIST>
-__global__ void __launch_bounds__(256, (D == 64 && !PERSIST) ? 4 : 2)
+template <int D, bool PERSIST, int KS>
+__global__ void __launch_bounds__(256 * KS, (D == 64 && !PERSIST) ? 4 : 2)
 dq_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
           const uint16_t *__restrict__ V, const uint16_t *__restrict__ O,
           const uint16_t *__restrict__ dO, const float *__restrict__ LSE,
@@ -360,11 +412,13 @@ dq_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
     // direct loads during the current item's last tile, its O rows and LSE
     // loaded into registers at the same time.
     constexpr bool kRowStage = PERSIST;
-    __shared__ __attribute__((aligned(1024))) uint16_t lds[2 * T::STAGE + (kRowStage ? 2 * T::BM * D : 0)];
+    __shared__ __attribute__((aligned(1024))) uint16_t lds_all[KS * 2 * T::STAGE + (kRowStage ? 2 * T::BM * D : 0)];
 
     const bool causal = causal_i != 0;
     const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
+    const int group = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8);
+    const int wave = (tid >> 6) & 3, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
+    uint16_t *const lds = lds_all + group * 2 * T::STAGE;
     const long long rs = static_cast<long long>(H) * D;
     const int n_items = nqb * B * H;
     const int G = static_cast<int>(gridDim.x);
@@ -433,7 +487,7 @@ dq_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
         my_delta = part + __shfl_xor(part, 32);
         const float lse2 = lse_in * kLog2e;
         neg_lse2 = -lse2;
-        if (q < L && g == 0) {
+        if (q < L && g == 0 && group == 0) {
             const long long wrow = static_cast<long long>(x.bh) * L;
             ndeltag[wrow + q] = -my_delta;
             lse2g[wrow + q] = lse2;
@@ -637,8 +691,10 @@ dq_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
 #pragma unroll
     for (int db = 0; db < DB; ++db)
         dq[db] = f32x16{};
-    int t = it.t_begin;
-    issue(it, t, lds);
+    int t = it.t_begin + group;
+    // (with KS > 1, a group's tile past the last is neither loaded nor used)
+    if (KS == 1 || t <= it.t_end)
+        issue(it, t, lds);
     wait_vmem();
     __syncthreads();
 
@@ -647,10 +703,11 @@ dq_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
     auto step = [&](auto bufc) __attribute__((always_inline)) -> bool {
         constexpr int BUF = decltype(bufc)::value;
         uint16_t *other = lds + (1 - BUF) * T::STAGE;
-        const bool last = t == it.t_end;
+        const bool last = t - group + KS > it.t_end;
         bool more = false;
         if (!last) {
-            issue(it, t + 1, other);
+            if (KS == 1 || t + KS <= it.t_end)
+                issue(it, t + KS, other);
         } else if constexpr (PERSIST) {
             const int nbid = item_bid(k_item + 1, static_cast<int>(blockIdx.x), G, n_items);
             more = nbid >= 0;
@@ -670,7 +727,8 @@ dq_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
                 }
             }
         }
-        compute(t, bufc);
+        if (KS == 1 || t <= it.t_end)
+            compute(t, bufc);
         if (!kRowStage && more)  // Q, dO, O rows of the next item (registers free after the tile)
             load_rows(nit);
         wait_vmem();
@@ -688,7 +746,7 @@ dq_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
             __syncthreads();
         }
         if (!last) {
-            ++t;
+            t += KS;
             return true;
         }
         if constexpr (!PERSIST) {
@@ -714,6 +772,9 @@ dq_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
         if (!step(IC<1>{}))
             break;
     }
+    if constexpr (KS > 1)
+        if (!add_group_sums<KS, DB>(lds_all, group, tid, dq))
+            return;
     if constexpr (!PERSIST)
         store();
 }
@@ -731,13 +792,51 @@ dq_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
         const uint16_t *__restrict__, const uint16_t *__restrict__, const float *__restrict__,   \
         float *__restrict__, float *__restrict__, uint16_t *__restrict__, int, int, int, int,     \
         const int32_t *__restrict__, int, float, float, int, RopeEpi, int
-template __global__ void dkdv1_kernel<64, false>(DD_KV_ARGS);  // D = 64: single-role waves
-template __global__ void dkdv1_kernel<64, true>(DD_KV_ARGS);
-template __global__ void dq_kernel<64, false>(DD_Q_ARGS);
-template __global__ void dq_kernel<64, true>(DD_Q_ARGS);
-template __global__ void dq_kernel<128, false>(DD_Q_ARGS);  // D = 128: never persistent
+template __global__ void dkdv1_kernel<64, false, 1>(DD_KV_ARGS);  // D = 64: single-role waves
+template __global__ void dkdv1_kernel<64, true, 1>(DD_KV_ARGS);
+template __global__ void dkdv1_kernel<64, false, 2>(DD_KV_ARGS);
+template __global__ void dq_kernel<64, false, 1>(DD_Q_ARGS);
+template __global__ void dq_kernel<64, true, 1>(DD_Q_ARGS);
+template __global__ void dq_kernel<64, false, 2>(DD_Q_ARGS);
+template __global__ void dq_kernel<64, false, 4>(DD_Q_ARGS);
+template __global__ void dq_kernel<128, false, 1>(DD_Q_ARGS);  // D = 128: never persistent
+template __global__ void dq_kernel<128, false, 2>(DD_Q_ARGS);
 #undef DD_KV_ARGS
 #undef DD_Q_ARGS
+
+// Groups of waves over which a block's tiles are split.  The workgroups of a
+// small grid are all resident at once, so the heaviest causal block's chain of
+// L / 64 tiles is the launch's time, and the groups shorten it; dispatch (or
+// the persistent forms' walk, at L <= 2048) balances larger grids, and the
+// groups only cost them their final sum.
+//
+// dQ, measured whole backward, us with 1 / 2 / 4 groups, D = 64: 32 blocks of
+// L = 1000 51 / 44 / 44.5, 256 of L = 512 31.1 / 30.4 / 33.2, 480 of L = 300
+// 31.4 / 32.2 / 41.4, 512 of L = 1024 63.8 / 62.2 / 72.6, 768 of L = 1024 85 /
+// 91 / 106, 1024 of L = 2048 165 / 176 / 193; 256 of L = 8192 292 / 249 / 237,
+// 512 of L = 8192 320 / 297 / 287, 1024 of L = 4096 330 / 293 / 303, 2048 of
+// L = 8192 961 / 942 / 955.  D = 128: 384 of L = 3000 184 / 156, 564 of L =
+// 6000 438 / 400, 1024 of L = 8192 898 / 892, 256 of L = 1024 68.8 / 65.7, 256
+// of L = 256 31.5 / 33.5, 512 of L = 2048 183 / 185.5.
+template <int D>
+static int dq_key_groups(long long blocks, int L)
+{
+    const long long cus = device_cu_count();
+    if (D == 64)
+        return L > 2048 ? (blocks <= 2 * cus ? 4 : blocks <= 8 * cus ? 2 : 1)
+                        : (blocks <= 2 * cus ? 2 : 1);
+    return (L > 2048 && blocks <= 4 * cus) || (L > 768 && blocks <= cus) ? 2 : 1;
+}
+
+// dK/dV at D = 64, 1 / 2 groups: 64 blocks of L = 2048 81 / 70, 256 of L = 512
+// 31.1 / 28.8, 512 of L = 8192 320 / 280, 512 of L = 1024 63.8 / 68.7, 480 of
+// L = 300 31.4 / 36.2, 768 of L = 2048 135.7 / 135.4, 1024 of L = 8192 514 /
+// 522.  (At D = 128 the paired waves fill a CU's registers with one group.)
+static int dkdv_query_groups(long long blocks, int L)
+{
+    const long long cus = device_cu_count();
+    return blocks <= cus || (L > 2048 && blocks <= 3 * cus) ? 2 : 1;
+}
 
 // ---------------------------------------------------------------------------
 template <int D>
@@ -773,15 +872,20 @@ static int launch_bwd_d(const BwdArgs &a)
         long long pgrid = 0;
         if constexpr (D == 64)
             if (a.L <= kDqPersistMaxSpan)
-                pgrid = persistent_grid<dq_kernel<D, true>>(256);
+                pgrid = persistent_grid<dq_kernel<D, true, 1>>(256);
         const bool persist = pgrid > 0 && pgrid < all;
-        auto kern = dq_kernel<D, false>;
-        if constexpr (D == 64)
-            if (persist)
-                kern = dq_kernel<D, true>;
+        const int ks = dq_key_groups<D>(static_cast<long long>(nqb) * a.B * a.H, a.L);
+        auto kern = ks == 2 ? dq_kernel<D, false, 2> : dq_kernel<D, false, 1>;
+        if constexpr (D == 64) {
+            if (ks == 4)
+                kern = dq_kernel<D, false, 4>;
+            else if (persist && ks == 1)
+                kern = dq_kernel<D, true, 1>;
+        }
         ProfScope prof(K_DQ, st);
         e = launch_kernel(kern,
-                          dim3(static_cast<unsigned>(persist ? pgrid : all)), dim3(256), st, a.Q,
+                          dim3(static_cast<unsigned>(persist && ks == 1 ? pgrid : all)),
+                          dim3(256 * ks), st, a.Q,
                           a.K, a.V, a.O, a.dO, a.LSE, lse2, ndelta, a.dQ, a.B, a.L, a.H,
                           a.causal ? 1 : 0, a.cu, a.n_docs, s.scale_log2, s.scale, nqb, s.rt,
                           s.rope);
@@ -799,12 +903,15 @@ static int launch_bwd_d(const BwdArgs &a)
             // Persistent for short rows, as many workgroups as are resident
             // at once (two per CU).
             const long long pgrid = a.L <= kPersistMaxSpan
-                                        ? persistent_grid<dkdv1_kernel<D, true>>(64 * T::NW)
+                                        ? persistent_grid<dkdv1_kernel<D, true, 1>>(64 * T::NW)
                                         : 0;
             const bool persist = pgrid > 0 && pgrid < all;
-            auto kern = persist ? dkdv1_kernel<D, true> : dkdv1_kernel<D, false>;
-            const long long grid = persist ? pgrid : all;
-            e = launch_kernel(kern, dim3(static_cast<unsigned>(grid)), dim3(64 * T::NW), st, a.Q,
+            const int ks = dkdv_query_groups(n_items, a.L);
+            auto kern = ks == 2   ? dkdv1_kernel<D, false, 2>
+                        : persist ? dkdv1_kernel<D, true, 1>
+                                  : dkdv1_kernel<D, false, 1>;
+            const long long grid = persist && ks == 1 ? pgrid : all;
+            e = launch_kernel(kern, dim3(static_cast<unsigned>(grid)), dim3(64 * T::NW * ks), st, a.Q,
                               a.K, a.V, a.dO, lse2, ndelta, a.dK, a.dV, a.B, a.L, a.H,
                               a.causal ? 1 : 0, a.cu, a.n_docs, s.scale_log2, s.scale, nkb, s.rt,
                               s.rope);

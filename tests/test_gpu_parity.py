@@ -42,7 +42,7 @@ def test_document_masked_chunks(cuda, D, causal):
 # Small grids split a block's tiles over groups of waves (two, or four in the
 # D = 64 forward from L = 769 on): tile counts that the groups do not divide,
 # blocks with fewer tiles than groups, groups whose keys are all masked.
-@pytest.mark.parametrize("L,D", [(768, 64), (769, 64), (1153, 64), (641, 128), (2177, 128)])
+@pytest.mark.parametrize("L,D", [(768, 64), (769, 64), (1153, 64), (641, 128), (2177, 128), (2177, 64)])
 @pytest.mark.parametrize("mode", ["causal", "full", "docs"])
 def test_small_grids_split_over_wave_groups(cuda, L, D, mode):
     cu = None
