@@ -111,7 +111,7 @@ dkdv1_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
     const bool causal = causal_i != 0;
     const int tid = threadIdx.x;
     const int group = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8);
-    const int wave = (tid >> 6) & 3, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
+    const int wave = KS == 1 ? tid >> 6 : (tid >> 6) & 3, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
     uint16_t *const lds = lds_all + group * 2 * T::STAGE;
     const long long rs = static_cast<long long>(H) * D;
     const int n_items = nkb * B * H;
@@ -290,7 +290,7 @@ dkdv1_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
     auto step = [&](auto bufc) __attribute__((always_inline)) -> bool {
         constexpr int BUF = decltype(bufc)::value;
         uint16_t *other = lds + (1 - BUF) * T::STAGE;
-        const bool last = t - group + KS > it.t_end;
+        const bool last = KS == 1 ? t == it.t_end : t - group + KS > it.t_end;
         bool more = false;
         if (!last) {
             if (KS == 1 || t + KS <= it.t_end)
@@ -417,7 +417,7 @@ dq_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
     const bool causal = causal_i != 0;
     const int tid = threadIdx.x;
     const int group = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8);
-    const int wave = (tid >> 6) & 3, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
+    const int wave = KS == 1 ? tid >> 6 : (tid >> 6) & 3, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
     uint16_t *const lds = lds_all + group * 2 * T::STAGE;
     const long long rs = static_cast<long long>(H) * D;
     const int n_items = nqb * B * H;
@@ -703,7 +703,7 @@ dq_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
     auto step = [&](auto bufc) __attribute__((always_inline)) -> bool {
         constexpr int BUF = decltype(bufc)::value;
         uint16_t *other = lds + (1 - BUF) * T::STAGE;
-        const bool last = t - group + KS > it.t_end;
+        const bool last = KS == 1 ? t == it.t_end : t - group + KS > it.t_end;
         bool more = false;
         if (!last) {
             if (KS == 1 || t + KS <= it.t_end)
