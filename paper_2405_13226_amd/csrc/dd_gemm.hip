@@ -126,11 +126,35 @@ struct GemmOperands {
 };
 
 // Sizes: M x N per group, K per segment; k_len of a split (segs * K without
-// splits); tiles_n = tile columns of all groups.
+// splits); tiles_n = tile columns of all groups; xm: tile_of.
 struct GemmSizes {
-    int M, N, K, k_len, tiles_n;
+    int M, N, K, k_len, tiles_n, xm;
     long long lda, ldb, ldc;
 };
+
+// Tile of block `id`.  Workgroups are dispatched round-robin over the 8 XCDs
+// (block id % 8), each with its own L2.  XCD x takes every xm-th tile row
+// from row x % xm on and one of 8 / xm blocks of columns, in bands of kGR of
+// its rows; a band is walked in groups of 32 tiles (one per CU of the XCD),
+// each group column by column, so the tiles that run at the same time share
+// their A and B panels in one L2.  xm = 0: row by row (tile_rows_step).
+constexpr int kGR = 4;
+
+__device__ __forceinline__ void tile_of(int id, int tiles_m, int tiles_n, int xm, int &tm, int &tn)
+{
+    if (xm == 0) {
+        tm = id / tiles_n;
+        tn = id - tm * tiles_n;
+        return;
+    }
+    const int x = id % kXcds, k = id / kXcds;
+    const int rows_x = tiles_m / xm, cols_x = tiles_n * xm / kXcds;
+    const int band = k / (kGR * cols_x), rem = k - band * kGR * cols_x;
+    const int gr = min(kGR, rows_x - band * kGR);  // rows of this band
+    const int gc = 32 / gr, grp = rem / (gr * gc), w = rem - grp * gr * gc;
+    tm = (band * kGR + w % gr) * xm + x % xm;
+    tn = x / xm * cols_x + grp * gc + w / gr;
+}
 
 // LDS position (elements) of the four columns c .. c + 3 of row r of the
 // finished BM x BN bf16 tile.  With kEpiSwiglu the column halves are two
@@ -235,26 +259,8 @@ gemm_kernel(GemmOperands op, GemmSizes sz)
     const int l16 = lane & 15, g = lane >> 4;
     const int wm = wave >> 2, wn = wave & 3;
     const int tiles_n = sz.tiles_n;
-    // Workgroups are dispatched round-robin over the 8 XCDs (block id % 8),
-    // each with its own L2.  Without a K split, XCD x takes the tile rows x,
-    // x + 8, ..., in bands of kGR of its rows; a band is walked in groups of
-    // kGC columns, each group column by column (kGR x kGC = 32 tiles, one
-    // per CU of the XCD), so the tiles that run at the same time share kGR
-    // A panels and kGC B panels in one L2.
     int tm, tn;
-    if (gridDim.y == 1 && (sz.M / T::BM) % kXcds == 0) {
-        constexpr int kGR = 4, kGC = 8;
-        const int x = static_cast<int>(blockIdx.x) % kXcds, k = static_cast<int>(blockIdx.x) / kXcds;
-        const int rows_x = (sz.M / T::BM) / kXcds;
-        const int band = k / (kGR * tiles_n), rem = k % (kGR * tiles_n);
-        const int gr = min(kGR, rows_x - band * kGR);  // rows of this band
-        const int grp_c = rem / (gr * kGC), w = rem % (gr * kGC);
-        tm = (band * kGR + w % gr) * kXcds + x;
-        tn = grp_c * kGC + w / gr;
-    } else {
-        tm = static_cast<int>(blockIdx.x) / tiles_n;
-        tn = static_cast<int>(blockIdx.x) % tiles_n;
-    }
+    tile_of(static_cast<int>(blockIdx.x), sz.M / T::BM, tiles_n, sz.xm, tm, tn);
     // Columns of one matrix B[g] (C[g]) in a tile.
     constexpr int NC = EPI == kEpiSwiglu ? T::BN / 2 : T::BN;
     const int m0 = tm * T::BM, tpg = sz.N / NC, grp = tn / tpg, n0 = (tn - grp * tpg) * NC;
@@ -524,18 +530,9 @@ gemm_mid_kernel(GemmOperands op, GemmSizes sz)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int l16 = lane & 15, g = lane >> 4;
     const int wm = wave / WN, wn = wave % WN, group = wave >> 2;
-    // Tile rows x, x + 8, ... on XCD x where the rows divide over the XCDs.
-    const int tiles_m = sz.M / T::BM, tiles_n = sz.tiles_n;
+    const int tiles_n = sz.tiles_n;
     int tm, tn;
-    if (gridDim.y == 1 && tiles_m % kXcds == 0) {
-        const int x = static_cast<int>(blockIdx.x) % kXcds, k = static_cast<int>(blockIdx.x) / kXcds;
-        const int rows_x = tiles_m / kXcds;
-        tm = (k % rows_x) * kXcds + x;
-        tn = k / rows_x;
-    } else {
-        tm = static_cast<int>(blockIdx.x) / tiles_n;
-        tn = static_cast<int>(blockIdx.x) % tiles_n;
-    }
+    tile_of(static_cast<int>(blockIdx.x), sz.M / T::BM, tiles_n, sz.xm, tm, tn);
     // Columns of one matrix B[g] (C[g]) in a tile.
     constexpr int NC = EPI == kEpiSwiglu ? T::BN / 2 : T::BN;
     const int m0 = tm * T::BM, tpg = sz.N / NC, grp = tn / tpg, n0 = (tn - grp * tpg) * NC;
@@ -807,6 +804,28 @@ GemmPlan gemm_plan(int M, long long N, long long K, bool may_split)
     }
 }
 
+// xm of tile_of: the one whose groups of 32 tiles read the fewest panels per
+// tile, of those that divide the tiles evenly (0: none does).  Eight tile rows
+// of a weight gradient, taken a row per XCD, read 24 B panels for 24 tiles
+// (2048 x 6144, K = 16,384: 430 us); as 4 x 6 tiles per XCD 400 us.
+static int tile_rows_step(int tiles_m, int tiles_n)
+{
+    int best = 0;
+    double least = 0;
+    for (int xm = kXcds; xm >= 1; xm /= 2) {
+        if (tiles_m % xm || tiles_n * xm % kXcds)
+            continue;
+        const double gr = std::min(kGR, tiles_m / xm);
+        const double gc = std::min(32 / gr, static_cast<double>(tiles_n * xm / kXcds));
+        const double panels = (gr + gc) / (gr * gc);
+        if (best == 0 || panels < least) {
+            best = xm;
+            least = panels;
+        }
+    }
+    return best;
+}
+
 size_t gemm_workspace_bytes(int M, int N, int K, int groups)
 {
     const GemmPlan p = gemm_plan(M, static_cast<long long>(groups) * N, K, true);
@@ -835,7 +854,8 @@ int launch_gemm(const GemmArgs &a)
     op.V = static_cast<const uint16_t *>(a.V);
     op.P = static_cast<float *>(a.workspace);
     const int tiles_n = static_cast<int>(cols / bn);
-    const GemmSizes sz{a.M, a.N, a.K, a.K / splits * a.segs, tiles_n, a.lda, a.ldb, a.ldc};
+    const GemmSizes sz{a.M, a.N, a.K, a.K / splits * a.segs, tiles_n,
+                       tile_rows_step(a.M / bm, tiles_n), a.lda, a.ldb, a.ldc};
     const dim3 grid(static_cast<unsigned>(a.M / bm) * tiles_n, static_cast<unsigned>(splits));
     const bool wide = a.lda >= kGemmWideStride || a.ldb >= kGemmWideStride;
     auto pick = [&](auto ta, auto tb, auto epi) {
