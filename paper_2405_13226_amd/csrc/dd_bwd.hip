@@ -135,10 +135,7 @@ dkdv1_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
         if (k_ok)
             key_queries(x.b, L, my_k, causal, cu, n_docs, qlo_k, qhi_k);
         wave_on = k0w < L;
-        lo_w = wave_min(k_ok ? qlo_k : 0x7fffffff);
-        hi_w = wave_max(k_ok ? qhi_k : -1);
-        lo_all = wave_max(k_ok ? qlo_k : -1);
-        hi_all = wave_min(k_ok ? qhi_k : 0x7fffffff);
+        wave_bounds(qlo_k, qhi_k, k0w, L, lo_w, hi_w, lo_all, hi_all);
         wave_full_keys = (k0w + 31) < L;
     };
 
@@ -271,6 +268,11 @@ dkdv1_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
         }
     };
 
+    // The first tile's loads are under way while the rows arrive.
+    int t = it.t_begin + group;
+    // (with KS = 2, a group's tile past the last is neither loaded nor used)
+    if (KS == 1 || t <= it.t_end)
+        kv_issue<D, T>(plan, lds, Q, dO, lse2g, ndeltag, it, t, L, rs, wave, lane);
     setup(it);
     load_kv(it);
 #pragma unroll
@@ -278,10 +280,6 @@ dkdv1_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
         dk[db] = f32x16{};
         dv[db] = f32x16{};
     }
-    int t = it.t_begin + group;
-    // (with KS = 2, a group's tile past the last is neither loaded nor used)
-    if (KS == 1 || t <= it.t_end)
-        kv_issue<D, T>(plan, lds, Q, dO, lse2g, ndeltag, it, t, L, rs, wave, lane);
     wait_vmem();
     __syncthreads();
 
@@ -441,10 +439,7 @@ dq_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
         if (q_ok)
             query_keys(x.b, L, my_q, causal, cu, n_docs, lo_q, hi_q);
         wave_on = q0w < L;
-        lo_w = wave_min(q_ok ? lo_q : 0x7fffffff);
-        hi_w = wave_max(q_ok ? hi_q : -1);
-        lo_all = wave_max(q_ok ? lo_q : -1);
-        hi_all = wave_min(q_ok ? hi_q : 0x7fffffff);
+        wave_bounds(lo_q, hi_q, q0w, L, lo_w, hi_w, lo_all, hi_all);
         wave_full_rows = (q0w + 31) < L;
     };
 
@@ -685,16 +680,17 @@ dq_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
             store_block_bf16(dQb + db * 32, dq[db], scale, g, q_ok);
     };
 
+    // The first tile's loads are under way while the rows arrive.
+    int t = it.t_begin + group;
+    // (with KS > 1, a group's tile past the last is neither loaded nor used)
+    if (KS == 1 || t <= it.t_end)
+        issue(it, t, lds);
     setup(it);
     load_rows(it);
     finish_rows(it);
 #pragma unroll
     for (int db = 0; db < DB; ++db)
         dq[db] = f32x16{};
-    int t = it.t_begin + group;
-    // (with KS > 1, a group's tile past the last is neither loaded nor used)
-    if (KS == 1 || t <= it.t_end)
-        issue(it, t, lds);
     wait_vmem();
     __syncthreads();
 

@@ -30,7 +30,6 @@
 #include "dd_launch.hpp"
 #include "dd_tile.hpp"
 
-#include <climits>
 
 namespace dd {
 
@@ -253,8 +252,10 @@ bwd_short_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
     int qlo_k = 1, qhi_k = 0;
     if (k_ok)
         key_queries(b, L, my_k, causal, cu, n_docs, qlo_k, qhi_k);
-    const int lo_w = wave_min(k_ok ? qlo_k : INT_MAX);
-    const int hi_w = wave_max(k_ok ? qhi_k : -1);
+    int lo_w, hi_w, lo_all, hi_all;
+    wave_bounds(qlo_k, qhi_k, wave * 32, L, lo_w, hi_w, lo_all, hi_all);
+    if (wave * 32 >= L)
+        hi_w = -1;  // no keys: every tile is skipped
 
     ShortOffsets o;
     o.init(lane);
@@ -459,8 +460,10 @@ bwd_short_persist_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restr
         int qlo_k = 1, qhi_k = 0;
         if (k_ok)
             key_queries(b, L, my_k, causal, cu, n_docs, qlo_k, qhi_k);
-        const int lo_w = wave_min(k_ok ? qlo_k : INT_MAX);
-        const int hi_w = wave_max(k_ok ? qhi_k : -1);
+        int lo_w, hi_w, lo_all, hi_all;
+        wave_bounds(qlo_k, qhi_k, wave * 32, L, lo_w, hi_w, lo_all, hi_all);
+        if (wave * 32 >= L)
+            hi_w = -1;  // no keys: every tile is skipped
 
         f32x16 dk[DB], dv[DB];
 #pragma unroll

@@ -92,10 +92,7 @@ dkdv_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
         if (k_ok)
             key_queries(x.b, L, my_k, causal, cu, n_docs, qlo_k, qhi_k);
         wave_on = k0w < L;
-        lo_w = wave_min(k_ok ? qlo_k : 0x7fffffff);
-        hi_w = wave_max(k_ok ? qhi_k : -1);
-        lo_all = wave_max(k_ok ? qlo_k : -1);
-        hi_all = wave_min(k_ok ? qhi_k : 0x7fffffff);
+        wave_bounds(qlo_k, qhi_k, k0w, L, lo_w, hi_w, lo_all, hi_all);
         wave_full_keys = (k0w + 31) < L;
     };
 
@@ -321,13 +318,14 @@ dkdv_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
             store_block_bf16(dst + db * 32, acc[db], osc, g, k_ok);
     };
 
+    // The first tile's loads are under way while the rows arrive.
+    int t = it.t_begin;
+    kv_issue<D, T>(plan, lds, Q, dO, lse2g, ndeltag, it, t, L, rs, wave, lane);
     setup(it);
     load_kv(it);
 #pragma unroll
     for (int db = 0; db < DB; ++db)
         acc[db] = f32x16{};
-    int t = it.t_begin;
-    kv_issue<D, T>(plan, lds, Q, dO, lse2g, ndeltag, it, t, L, rs, wave, lane);
     wait_vmem();
     __syncthreads();
 
