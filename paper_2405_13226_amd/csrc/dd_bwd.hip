@@ -23,10 +23,12 @@
 //             read them row-wise, dV^T and dK^T transposed (ds_read_b64_tr_b16).
 // Splitting dQ from dK/dV keeps every output owned by exactly one workgroup:
 // no atomics, deterministic results, at the cost of recomputing S and dP.
-// At D = 64, rows of at most 256 tokens without RoPE instead take one launch
+// On grids of few blocks both run at once in one launch (bwd_together).  At D
+// = 64, rows of at most 256 tokens without RoPE otherwise take one launch
 // (dd_bwd_short.hip) in which a slice fits one workgroup and S and dP are
 // formed once.
 #include "dd_bwd.hpp"
+#include "dd_dkdv.hpp"
 #include "dd_tile.hpp"
 #include "dd_launch.hpp"
 #include "dd_prof.hpp"
@@ -95,13 +97,13 @@ struct KvTile1 {
 // every other query tile of the same 128 keys, with LDS stages of its own;
 // its dK and dV are added through LDS at the end (dkdv_query_groups).
 template <int D, bool PERSIST, int KS>
-__global__ void __launch_bounds__(256 * KS, 2)
-dkdv1_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
-             const uint16_t *__restrict__ V, const uint16_t *__restrict__ dO,
-             const float *__restrict__ lse2g, const float *__restrict__ ndeltag,
-             uint16_t *__restrict__ dK, uint16_t *__restrict__ dV, int B, int L, int H,
-             int causal_i, const int32_t *__restrict__ cu, int n_docs, float scale_log2,
-             float scale, int nkb, RopeEpi rt, int rope)
+__device__ __forceinline__ void
+dkdv1_body(int wg, int G, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
+           const uint16_t *__restrict__ V, const uint16_t *__restrict__ dO,
+           const float *__restrict__ lse2g, const float *__restrict__ ndeltag,
+           uint16_t *__restrict__ dK, uint16_t *__restrict__ dV, int B, int L, int H,
+           int causal_i, const int32_t *__restrict__ cu, int n_docs, float scale_log2,
+           float scale, int nkb, RopeEpi rt, int rope)
 {
     using T = KvTile1<D>;
     constexpr int KK = D / 16;
@@ -115,10 +117,9 @@ dkdv1_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
     uint16_t *const lds = lds_all + group * 2 * T::STAGE;
     const long long rs = static_cast<long long>(H) * D;
     const int n_items = nkb * B * H;
-    const int G = static_cast<int>(gridDim.x);
 
     int k_item = 0;
-    const int bid = item_bid(0, static_cast<int>(blockIdx.x), G, n_items);
+    const int bid = item_bid(0, wg, G, n_items);
     if (bid < 0)
         return;
     KvItem it = kv_item<D, T>(bid, nkb, B, L, H, causal, cu, n_docs), nit = it;
@@ -294,7 +295,7 @@ dkdv1_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
             if (KS == 1 || t + KS <= it.t_end)
                 kv_issue<D, T>(plan, other, Q, dO, lse2g, ndeltag, it, t + KS, L, rs, wave, lane);
         } else if constexpr (PERSIST) {
-            const int nbid = item_bid(k_item + 1, static_cast<int>(blockIdx.x), G, n_items);
+            const int nbid = item_bid(k_item + 1, wg, G, n_items);
             more = nbid >= 0;
             if (more) {
                 nit = kv_item<D, T>(nbid, nkb, B, L, H, causal, cu, n_docs);
@@ -338,6 +339,19 @@ dkdv1_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
         if (!step(IC<1>{}))
             break;
     }
+}
+
+template <int D, bool PERSIST, int KS>
+__global__ void __launch_bounds__(256 * KS, 2)
+dkdv1_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
+             const uint16_t *__restrict__ V, const uint16_t *__restrict__ dO,
+             const float *__restrict__ lse2g, const float *__restrict__ ndeltag,
+             uint16_t *__restrict__ dK, uint16_t *__restrict__ dV, int B, int L, int H,
+             int causal_i, const int32_t *__restrict__ cu, int n_docs, float scale_log2,
+             float scale, int nkb, RopeEpi rt, int rope)
+{
+    dkdv1_body<D, PERSIST, KS>(blockIdx.x, gridDim.x, Q, K, V, dO, lse2g, ndeltag, dK, dV, B, L,
+                               H, causal_i, cu, n_docs, scale_log2, scale, nkb, rt, rope);
 }
 
 // ---------------------------------------------------------------------------
@@ -393,15 +407,21 @@ __device__ __forceinline__ QItem q_item(int bid, int nqb, int B, int L, int H, b
 // own; the groups' dQ are added through LDS at the end (dq_key_groups).
 // Waves per SIMD: four in the one-block D = 64 form (at most 128 VGPRs),
 // two otherwise (the persistent form's item loop and D = 128 need more).
+// LDS elements of a workgroup (1 KiB aligned): KS groups' stages and, when
+// persistent, the staged rows.
 template <int D, bool PERSIST, int KS>
-__global__ void __launch_bounds__(256 * KS, (D == 64 && !PERSIST) ? 4 : 2)
-dq_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
-          const uint16_t *__restrict__ V, const uint16_t *__restrict__ O,
-          const uint16_t *__restrict__ dO, const float *__restrict__ LSE,
-          float *__restrict__ lse2g, float *__restrict__ ndeltag,
-          uint16_t *__restrict__ dQ, int B, int L, int H, int causal_i,
-          const int32_t *__restrict__ cu, int n_docs, float scale_log2, float scale, int nqb,
-          RopeEpi rt, int rope)
+constexpr int kDqLds = KS * 2 * QTile<D>::STAGE + (PERSIST ? 2 * QTile<D>::BM * D : 0);
+
+// ROWS: writes -delta and the log2-LSE of its rows for dK/dV.
+template <int D, bool PERSIST, int KS, bool ROWS>
+__device__ __forceinline__ void
+dq_body(uint16_t *lds_all, int wg, int G, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
+        const uint16_t *__restrict__ V, const uint16_t *__restrict__ O,
+        const uint16_t *__restrict__ dO, const float *__restrict__ LSE,
+        float *__restrict__ lse2g, float *__restrict__ ndeltag,
+        uint16_t *__restrict__ dQ, int B, int L, int H, int causal_i,
+        const int32_t *__restrict__ cu, int n_docs, float scale_log2, float scale, int nqb,
+        RopeEpi rt, int rope)
 {
     using T = QTile<D>;
     constexpr int KK = D / 16;
@@ -410,7 +430,6 @@ dq_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
     // direct loads during the current item's last tile, its O rows and LSE
     // loaded into registers at the same time.
     constexpr bool kRowStage = PERSIST;
-    __shared__ __attribute__((aligned(1024))) uint16_t lds_all[KS * 2 * T::STAGE + (kRowStage ? 2 * T::BM * D : 0)];
 
     const bool causal = causal_i != 0;
     const int tid = threadIdx.x;
@@ -419,10 +438,9 @@ dq_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
     uint16_t *const lds = lds_all + group * 2 * T::STAGE;
     const long long rs = static_cast<long long>(H) * D;
     const int n_items = nqb * B * H;
-    const int G = static_cast<int>(gridDim.x);
 
     int k_item = 0;
-    const int bid = item_bid(0, static_cast<int>(blockIdx.x), G, n_items);
+    const int bid = item_bid(0, wg, G, n_items);
     if (bid < 0)
         return;
     QItem it = q_item<D>(bid, nqb, B, L, H, causal, cu, n_docs), nit = it;
@@ -482,7 +500,7 @@ dq_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
         my_delta = part + __shfl_xor(part, 32);
         const float lse2 = lse_in * kLog2e;
         neg_lse2 = -lse2;
-        if (q < L && g == 0 && group == 0) {
+        if (ROWS && q < L && g == 0 && group == 0) {
             const long long wrow = static_cast<long long>(x.bh) * L;
             ndeltag[wrow + q] = -my_delta;
             lse2g[wrow + q] = lse2;
@@ -705,7 +723,7 @@ dq_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
             if (KS == 1 || t + KS <= it.t_end)
                 issue(it, t + KS, other);
         } else if constexpr (PERSIST) {
-            const int nbid = item_bid(k_item + 1, static_cast<int>(blockIdx.x), G, n_items);
+            const int nbid = item_bid(k_item + 1, wg, G, n_items);
             more = nbid >= 0;
             if (more) {
                 nit = q_item<D>(nbid, nqb, B, L, H, causal, cu, n_docs);
@@ -775,6 +793,87 @@ dq_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
         store();
 }
 
+template <int D, bool PERSIST, int KS>
+__global__ void __launch_bounds__(256 * KS, (D == 64 && !PERSIST) ? 4 : 2)
+dq_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
+          const uint16_t *__restrict__ V, const uint16_t *__restrict__ O,
+          const uint16_t *__restrict__ dO, const float *__restrict__ LSE,
+          float *__restrict__ lse2g, float *__restrict__ ndeltag,
+          uint16_t *__restrict__ dQ, int B, int L, int H, int causal_i,
+          const int32_t *__restrict__ cu, int n_docs, float scale_log2, float scale, int nqb,
+          RopeEpi rt, int rope)
+{
+    __shared__ __attribute__((aligned(1024))) uint16_t lds[kDqLds<D, PERSIST, KS>];
+    dq_body<D, PERSIST, KS, true>(lds, blockIdx.x, gridDim.x, Q, K, V, O, dO, LSE, lse2g, ndeltag, dQ,
+                                  B, L, H, causal_i, cu, n_docs, scale_log2, scale, nqb, rt, rope);
+}
+
+// ---------------------------------------------------------------------------
+// Both at once, for grids that leave CUs idle one after the other: a first
+// kernel forms the softmax row terms, then one launch holds dK/dV's blocks
+// and dQ's, each of eight waves (two wave groups, or the paired waves of
+// dK/dV at D = 128).
+// ---------------------------------------------------------------------------
+
+// -delta and the LSE in log2 units of every (token, head) row: D / 8 lanes
+// per row, rows in memory order, results in the [B*H][L] workspace rows.
+template <int D>
+__global__ void __launch_bounds__(256)
+bwd_rows_kernel(const uint16_t *__restrict__ O, const uint16_t *__restrict__ dO,
+                const float *__restrict__ LSE, float *__restrict__ lse2g,
+                float *__restrict__ ndeltag, int L, int H, int rows)
+{
+    constexpr int LPR = D / 8;
+    const int row = (static_cast<int>(blockIdx.x) * 256 + static_cast<int>(threadIdx.x)) / LPR;
+    const int x = threadIdx.x % LPR;
+    if (row >= rows)
+        return;
+    const long long at = static_cast<long long>(row) * D + 8 * x;
+    const bf16x8 o = as_bf16x8(*reinterpret_cast<const u32x4 *>(O + at));
+    const bf16x8 d = as_bf16x8(*reinterpret_cast<const u32x4 *>(dO + at));
+    float part = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        part += static_cast<float>(o[i]) * static_cast<float>(d[i]);
+#pragma unroll
+    for (int m = 1; m < LPR; m *= 2)
+        part += __shfl_xor(part, m);
+    if (x == 0) {
+        const int t = row / H, h = row - t * H, b = t / L, q = t - b * L;
+        const long long to = (static_cast<long long>(b) * H + h) * L + q;
+        ndeltag[to] = -part;
+        lse2g[to] = LSE[row] * kLog2e;
+    }
+}
+
+template <int D>
+__global__ void __launch_bounds__(512, 2)
+bwd_pair_kernel(int kv_grid, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
+                const uint16_t *__restrict__ V, const uint16_t *__restrict__ O,
+                const uint16_t *__restrict__ dO, const float *__restrict__ LSE,
+                float *__restrict__ lse2g, float *__restrict__ ndeltag,
+                uint16_t *__restrict__ dQ, uint16_t *__restrict__ dK, uint16_t *__restrict__ dV,
+                int B, int L, int H, int causal_i, const int32_t *__restrict__ cu, int n_docs,
+                float scale_log2, float scale, int nblk, RopeEpi rt, int rope)
+{
+    // (one buffer for either; the D = 64 dK/dV work has its own)
+    constexpr int kKv = 2 * KvTile<D>::STAGE + 2 * KvTile<D>::PBUF_FLOATS;
+    constexpr int kDq = kDqLds<D, false, 2>;
+    __shared__ __attribute__((aligned(1024))) uint16_t lds[D == 64 || kDq > kKv ? kDq : kKv];
+    const int id = static_cast<int>(blockIdx.x);
+    if (id < kv_grid) {
+        if constexpr (D == 64)
+            dkdv1_body<D, false, 2>(id, kv_grid, Q, K, V, dO, lse2g, ndeltag, dK, dV, B, L, H,
+                                    causal_i, cu, n_docs, scale_log2, scale, nblk, rt, rope);
+        else
+            dkdv_body<D, false>(lds, reinterpret_cast<float *>(lds + 2 * KvTile<D>::STAGE), id, kv_grid, Q, K, V, dO, lse2g, ndeltag, dK, dV, B, L, H,
+                                causal_i, cu, n_docs, scale_log2, scale, nblk, rt, rope);
+    } else
+        dq_body<D, false, 2, false>(lds, id - kv_grid, gridDim.x - kv_grid, Q, K, V, O, dO, LSE, lse2g,
+                                    ndeltag, dQ, B, L, H, causal_i, cu, n_docs, scale_log2, scale,
+                                    nblk, rt, rope);
+}
+
 // Explicit instantiations: the host-side launch stubs of these kernel
 // templates are emitted here unconditionally (clang's host pass does not
 // always emit them for templates only referenced through a function pointer).
@@ -797,6 +896,26 @@ template __global__ void dq_kernel<64, false, 2>(DD_Q_ARGS);
 template __global__ void dq_kernel<64, false, 4>(DD_Q_ARGS);
 template __global__ void dq_kernel<128, false, 1>(DD_Q_ARGS);  // D = 128: never persistent
 template __global__ void dq_kernel<128, false, 2>(DD_Q_ARGS);
+template __global__ void bwd_rows_kernel<64>(const uint16_t *__restrict__,
+                                             const uint16_t *__restrict__,
+                                             const float *__restrict__, float *__restrict__,
+                                             float *__restrict__, int, int, int);
+template __global__ void bwd_pair_kernel<64>(
+    int, const uint16_t *__restrict__, const uint16_t *__restrict__, const uint16_t *__restrict__,
+    const uint16_t *__restrict__, const uint16_t *__restrict__, const float *__restrict__,
+    float *__restrict__, float *__restrict__, uint16_t *__restrict__, uint16_t *__restrict__,
+    uint16_t *__restrict__, int, int, int, int, const int32_t *__restrict__, int, float, float,
+    int, RopeEpi, int);
+template __global__ void bwd_rows_kernel<128>(const uint16_t *__restrict__,
+                                             const uint16_t *__restrict__,
+                                             const float *__restrict__, float *__restrict__,
+                                             float *__restrict__, int, int, int);
+template __global__ void bwd_pair_kernel<128>(
+    int, const uint16_t *__restrict__, const uint16_t *__restrict__, const uint16_t *__restrict__,
+    const uint16_t *__restrict__, const uint16_t *__restrict__, const float *__restrict__,
+    float *__restrict__, float *__restrict__, uint16_t *__restrict__, uint16_t *__restrict__,
+    uint16_t *__restrict__, int, int, int, int, const int32_t *__restrict__, int, float, float,
+    int, RopeEpi, int);
 #undef DD_KV_ARGS
 #undef DD_Q_ARGS
 
@@ -834,6 +953,27 @@ static int dkdv_query_groups(long long blocks, int L)
     return blocks <= cus || (L > 2048 && blocks <= 3 * cus) ? 2 : 1;
 }
 
+// Whether dK/dV and dQ run as one launch (bwd_pair_kernel; blocks of each).
+// Its workgroups fill a CU, so it pays while both kernels' blocks fit the chip
+// about once; longer rows, whose heaviest blocks take longer than the average
+// ones, gain up to 5 blocks per 4 CUs.  Measured, one after the other / both
+// at once, us.  D = 64: 32 blocks of L = 256 18.4 / 11.5 (the one-kernel
+// backward), 128 of L = 512 25.0 / 16.4, 144 of L = 700 31 / 23, 192 of L =
+// 300 20.7 / 20.7, 256 of L = 1024 37.7 / 39.5, 64 of L = 2048 60 / 36, 256 of
+// L = 8192 196 / 146, 320 of L = 5000 140 / 122, 512 of L = 4096 153 / 158.
+// D = 128: 32 of L = 256 25.4 / 16.9, 128 of L = 1024 60 / 39, 192 of L = 512
+// 41.5 / 42.9, 320 of L = 5000 245 / 199, 512 of L = 4096 248 / 259.  At D =
+// 64 the one-kernel backward keeps rows of at most 128 tokens (128 blocks of
+// L = 64: 8.1 / 9.0).
+template <int D>
+static bool bwd_together(long long blocks, int L, bool rope)
+{
+    if (D == 64 && !rope && L <= 128)
+        return false;
+    const long long cus = device_cu_count();
+    return 8 * blocks <= 5 * cus || (L > 1024 && 4 * blocks <= 5 * cus);
+}
+
 // ---------------------------------------------------------------------------
 template <int D>
 static int launch_bwd_d(const BwdArgs &a)
@@ -852,6 +992,23 @@ static int launch_bwd_d(const BwdArgs &a)
     s.rt = s.rope ? rope_epi(a.rope_base, D) : RopeEpi{};
 
     hipError_t e;
+    // Small grids: both kernels' blocks in one launch.
+    const int nblk = (a.L + QTile<D>::BM - 1) / QTile<D>::BM;
+    const long long blocks = static_cast<long long>(nblk) * a.B * a.H;
+    if (bwd_together<D>(blocks, a.L, s.rope != 0)) {
+        const int rows = a.B * a.L * a.H;
+        const int kv_grid = static_cast<int>((blocks + kXcds - 1) / kXcds * kXcds);
+        ProfScope prof(K_DKDV, st);
+        e = launch_kernel(bwd_rows_kernel<D>, dim3(static_cast<unsigned>((rows + 2048 / D - 1) / (2048 / D))),
+                          dim3(256), st, a.O, a.dO, a.LSE, lse2, ndelta, a.L, a.H, rows);
+        if (e != hipSuccess)
+            return DD_ERR_HIP;
+        e = launch_kernel(bwd_pair_kernel<D>, dim3(2 * kv_grid), dim3(512), st, kv_grid, a.Q, a.K,
+                          a.V, a.O, a.dO, a.LSE, lse2, ndelta, a.dQ, a.dK, a.dV, a.B, a.L, a.H,
+                          a.causal ? 1 : 0, a.cu, a.n_docs, s.scale_log2, s.scale, nblk, s.rt,
+                          s.rope);
+        return e == hipSuccess ? DD_OK : DD_ERR_HIP;
+    }
     if constexpr (D == 64)
         if (a.L <= kShortMaxRow && s.rope == 0) {
             ProfScope prof(K_BWD_SHORT, st);

@@ -40,16 +40,27 @@ def test_document_masked_chunks(cuda, D, causal):
 
 
 # Small grids split a block's tiles over groups of waves (two, or four in the
-# D = 64 forward from L = 769 on): tile counts that the groups do not divide,
-# blocks with fewer tiles than groups, groups whose keys are all masked.
-@pytest.mark.parametrize("L,D", [(768, 64), (769, 64), (1153, 64), (641, 128), (2177, 128), (2177, 64)])
+# D = 64 forward from L = 769 on) and run dK/dV and dQ in one launch: tile
+# counts that the groups do not divide, blocks with fewer tiles than groups,
+# groups whose keys are all masked, the shortest rows of the joint launch.
+@pytest.mark.parametrize("L,D", [(129, 64), (768, 64), (769, 64), (1153, 64), (2177, 64),
+                                 (65, 128), (641, 128), (2177, 128)])
 @pytest.mark.parametrize("mode", ["causal", "full", "docs"])
-def test_small_grids_split_over_wave_groups(cuda, L, D, mode):
+def test_small_grids(cuda, L, D, mode):
     cu = None
     if mode == "docs":
-        cu = dd.chunk_doclens([L // 3, 1, 70, L - L // 3 - 71], L)
+        cu = dd.chunk_doclens([L // 3, 1, 20, L - L // 3 - 21], L)
     check_case(1, L, 2, D, causal=mode != "full", cu=cu, seed=900 + L,
-               tag=f"wave groups L={L} D={D} {mode}")
+               tag=f"small grid L={L} D={D} {mode}")
+
+
+# Grids past the joint launch's range whose blocks are still split: dQ over two
+# groups (and four, D = 64 from L = 2049 on), dK/dV at D = 64 over two.
+@pytest.mark.parametrize("L,H,D", [(700, 32, 64), (1153, 40, 64), (2177, 20, 64), (900, 24, 128),
+                                   (2177, 20, 128)])
+def test_grids_of_split_blocks(cuda, L, H, D):
+    check_case(1, L, H, D, causal=True, seed=950 + L, bh=[(0, 0), (0, 7), (0, H - 1)],
+               tag=f"split blocks L={L} H={H} D={D}")
 
 
 # Short rows take the persistent forms of the forward, dK/dV and (D = 64) dQ
