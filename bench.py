@@ -690,8 +690,8 @@ def run_gemm(args, dev):
     from paper_2405_13226_amd.layer import OPENLM_1B
 
     T, d, hid = TOKENS, OPENLM_1B["d"], OPENLM_1B["hidden"]
-    # (name, M, N, K, trans_a, trans_b): y = x (W^T)^T (the block's forward
-    # reads transposed weight copies), dx = dy W^T, dW = x^T dy
+    # (name, M, N, K, trans_a, trans_b): y = x (W^T)^T (weights stored [N][K]),
+    # dx = dy W^T, dW = x^T dy
     shapes = [("qkv fwd", T, 3 * d, d, 0, 1), ("out fwd", T, d, d, 0, 1),
               ("w1 fwd", T, hid, d, 0, 1), ("w2 fwd", T, d, hid, 0, 1),
               ("qkv dx", T, d, 3 * d, 0, 1), ("w1 dx", T, d, hid, 0, 1),

@@ -267,11 +267,8 @@ int dd_swiglu_bwd(const void *U, const void *V, const void *dY, void *dU, void *
 
 /*
  * Y = X^T for a bf16 matrix X [rows, cols] (row stride ldx): Y [cols, rows]
- * (row stride ldy), Y[c][r] = X[r][c], bit-exact.  The block's forward
- * products read their weights through it (Sec. 3.1; Table "openlm1b": the
- * d x 3d, d x d, d x 5632 and 5632 x d projections), so that both operands
- * of every forward product are read row-wise.  rows, cols: multiples of 64,
- * rows * cols <= 2^36; ldx >= cols, ldy >= rows, both multiples of 8;
+ * (row stride ldy), Y[c][r] = X[r][c], bit-exact.  rows, cols: multiples of
+ * 64, rows * cols <= 2^36; ldx >= cols, ldy >= rows, both multiples of 8;
  * pointers 16-byte aligned; X and Y must not overlap.
  */
 int dd_transpose(const void *X, long long ldx, void *Y, long long ldy, int rows, int cols,
