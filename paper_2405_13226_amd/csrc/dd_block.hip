@@ -230,6 +230,35 @@ layernorm_param_grad_kernel(const float *__restrict__ sums, int d, uint16_t *__r
     *dst = __builtin_bit_cast(uint16_t, v);
 }
 
+// The same in one launch for at most kLnOneStage partial rows (2048 rows of
+// input): 16 waves sum 64 columns, wave w the rows w, w + 16, ....  The two
+// launches took 3.8 + 3.7 us there, mostly their own latency; this one 4.1.
+constexpr int kLnOneStage = 256;
+
+__global__ void __launch_bounds__(1024)
+layernorm_param_one_kernel(const float *__restrict__ part, int nparts, int d,
+                           uint16_t *__restrict__ dW, uint16_t *__restrict__ dB)
+{
+    __shared__ float red[16][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int col = static_cast<int>(blockIdx.x) * 64 + lane;  // 2 d is a multiple of 64
+    float s = 0.f;
+#pragma unroll 4
+    for (int p = wave; p < nparts; p += 16)
+        s += part[static_cast<long long>(p) * 2 * d + col];
+    red[wave][lane] = s;
+    __syncthreads();
+    if (wave == 0) {
+        float t = 0.f;
+#pragma unroll
+        for (int w = 0; w < 16; ++w)
+            t += red[w][lane];
+        const __bf16 v = static_cast<__bf16>(t);
+        uint16_t *dst = col < d ? dW + col : dB + (col - d);
+        *dst = __builtin_bit_cast(uint16_t, v);
+    }
+}
+
 // SwiGLU: y = silu(u) * v, silu(u) = u / (1 + exp(-u)); 8 elements per
 // thread, grid-stride.
 __global__ void __launch_bounds__(256)
@@ -329,6 +358,12 @@ int launch_layernorm_bwd(const LayerNormArgs &a)
     }
     if (e != hipSuccess)
         return DD_ERR_HIP;
+    if (nparts <= kLnOneStage) {
+        e = launch_kernel(layernorm_param_one_kernel, dim3(static_cast<unsigned>(2 * a.d / 64)),
+                          dim3(1024), st, static_cast<const float *>(part), nparts, a.d,
+                          static_cast<uint16_t *>(a.dw), static_cast<uint16_t *>(a.db));
+        return e == hipSuccess ? DD_OK : DD_ERR_HIP;
+    }
     float *sums = part + static_cast<long long>(nparts) * 2 * a.d;
     e = launch_kernel(layernorm_param_chunk_kernel,
                       dim3(static_cast<unsigned>((2 * a.d + 63) / 64), kLnChunks), dim3(256), st,

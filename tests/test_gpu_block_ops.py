@@ -167,7 +167,8 @@ def ln_ref(x, w, b, dy, dres, eps=1e-5):
     return y, dx, (dy * xh).sum(0), dy.sum(0), mu[:, 0], rstd[:, 0]
 
 
-@pytest.mark.parametrize("rows,d", [(100, 512), (777, 1024), (4096, 2048)])
+@pytest.mark.parametrize("rows,d", [(1, 512), (100, 512), (777, 1024), (2048, 1024), (2049, 1024),
+                                    (4096, 2048)])
 def test_layer_norm(cuda, rows, d):
     x = bf16((rows, d), rows, 2.0) + 0.5
     w, b = bf16((d,), 5) * 0.3 + 1, bf16((d,), 6) * 0.3
