@@ -438,7 +438,10 @@ gemm_kernel(GemmOperands op, GemmSizes sz)
     at.next(ka, kb);
     wait_and_barrier<8>();
     read_a(a0, 0, 0);
-    __builtin_amdgcn_sched_barrier(0);
+    // Phase 1 refills the half just read: as in the loop, only after a barrier
+    // that every wave reaches with its reads returned (a load of one wave
+    // writes rows that all the others read).
+    wait_and_barrier<8>();
     // The second group of four waves runs half a phase behind the first: on
     // every SIMD one wave issues products while the other reads and loads.
     if (wm == 1)

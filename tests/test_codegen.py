@@ -97,3 +97,20 @@ def test_attention_kernels_do_not_spill(src, tmp_path):
     if src in four_waves:
         sym = next(k for k in res if k.startswith(four_waves[src]))
         assert res[sym][0] <= 128, res[sym]
+
+
+def test_large_gemm_first_refill_waits_for_the_reads(tmp_path):
+    # The 256 x 256 GEMM kernels read A's first half before their loop, whose
+    # first loads refill that half: from the first LDS read on, every wave has
+    # to wait for its reads and meet the workgroup's barrier before any direct
+    # global->LDS load.
+    asm = device_asm("dd_gemm.hip", tmp_path)
+    syms = sorted(set(re.findall(r"^(_ZN2dd11gemm_kernelI\w+):", asm, re.M)))
+    assert len(syms) == 16  # eight operand forms and epilogues, narrow and wide
+    for sym in syms:
+        _, lines = kernel_body(asm, sym)
+        first = next(i for i, ln in enumerate(lines) if ln.startswith("ds_read"))
+        load = next(i for i in range(first, len(lines)) if lines[i].startswith("global_load_lds"))
+        ordered = any(a.startswith("s_waitcnt") and "lgkmcnt(0)" in a and b.startswith("s_barrier")
+                      for a, b in zip(lines[first:load], lines[first + 1:load]))
+        assert ordered, sym
