@@ -60,13 +60,22 @@ def gemm(a, b, trans_a: bool = False, trans_b: bool = False, residual=None, out=
     return out
 
 
-def _same(ts, name):
-    """Matrices of one shape and row stride; returns that stride."""
+def _shared_stride(ts, name):
+    """The row stride of matrices of one shape, or None where they differ."""
     for t in ts:
         _mat(t, name)
-        if t.shape != ts[0].shape or t.stride(0) != ts[0].stride(0):
-            raise ValueError(f"the {name} matrices must agree in shape and row stride")
-    return ts[0].stride(0)
+        if t.shape != ts[0].shape:
+            raise ValueError(f"the {name} matrices must agree in shape")
+    strides = {t.stride(0) for t in ts}
+    return strides.pop() if len(strides) == 1 else None
+
+
+def _same(ts, name):
+    """Matrices of one shape and row stride; returns that stride."""
+    ld = _shared_stride(ts, name)
+    if ld is None:
+        raise ValueError(f"the {name} matrices must agree in row stride")
+    return ld
 
 
 def _array(ts):
@@ -98,12 +107,18 @@ def gemm_group(a, bs, trans_a: bool = False, trans_b: bool = False, outs=None):
 
 def gemm_sum(as_, bs, trans_b: bool = False):
     """sum of a @ op(b) over the pairs of as_ and bs (at most three), summed in
-    fp32 and rounded once."""
-    lda, ldb = _same(as_, "a"), _same(bs, "b")
+    fp32 and rounded once.  The launch takes one row stride per side: where they
+    differ, the products run one by one, each rounded as it is added."""
+    lda, ldb = _shared_stride(as_, "a"), _shared_stride(bs, "b")
     M, K = as_[0].shape
     Kb, N = (bs[0].shape[1], bs[0].shape[0]) if trans_b else (bs[0].shape[0], bs[0].shape[1])
-    if K != Kb or len(as_) != len(bs):
-        raise ValueError("the pairs must agree in their inner dimension")
+    if K != Kb or len(as_) != len(bs) or len(as_) > 3:
+        raise ValueError("need at most three pairs that agree in their inner dimension")
+    if lda is None or ldb is None:
+        out = gemm(as_[0], bs[0], trans_b=trans_b)
+        for a, b in zip(as_[1:], bs[1:]):
+            gemm(a, b, trans_b=trans_b, residual=out, out=out)
+        return out
     out = torch.empty((M, N), dtype=torch.bfloat16, device=as_[0].device)
     st = lib().dd_gemm_sum(_array(as_), lda, _array(bs), ldb, int(bool(trans_b)), _p(out), N,
                            len(as_), M, N, K, _stream(out.device))
@@ -112,12 +127,16 @@ def gemm_sum(as_, bs, trans_b: bool = False):
 
 
 def gemm_swiglu(x, w1, w3):
-    """(u, v, silu(u) * v) with u = x @ w1 and v = x @ w3, in one launch."""
+    """(u, v, silu(u) * v) with u = x @ w1 and v = x @ w3, in one launch
+    (one each where the row strides of w1 and w3 differ)."""
     _mat(x, "x")
-    ldw = _same([w1, w3], "w")
+    ldw = _shared_stride([w1, w3], "w")
     (M, K), (Kw, N) = x.shape, w1.shape
     if K != Kw:
         raise ValueError(f"inner dimensions differ: {K} vs {Kw}")
+    if ldw is None:
+        u, v = gemm(x, w1), gemm(x, w3)
+        return u, v, swiglu(u, v)
     u, v, y = (torch.empty((M, N), dtype=torch.bfloat16, device=x.device) for _ in range(3))
     st = lib().dd_gemm_swiglu(_p(x), x.stride(0), _p(w1), _p(w3), ldw, _p(u), _p(v), _p(y), N,
                               M, N, K, _stream(x.device))

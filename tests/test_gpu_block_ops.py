@@ -143,6 +143,20 @@ def test_gemm_sum(cuda, M, N, K, n):
     assert rel_l2(f64(got), sum(f64(x) @ f64(v).T for x, v in zip(xs, ws))) <= RTOL
 
 
+def test_joint_products_of_different_row_strides(cuda):
+    # Weights whose strides differ run as one product each: the sum then rounds
+    # after every addition, the rest is bit for bit the same.
+    M, N, K = 256, 512, 256
+    x, w1 = bf16((M, K), 1).to(cuda), bf16((K, N), 2, 0.1).to(cuda)
+    w3 = bf16((K, N + 256), 3, 0.1).to(cuda)[:, :N]
+    same = [w1, w3.contiguous()]
+    for got, want in zip(ops.gemm_swiglu(x, w1, w3), ops.gemm_swiglu(x, *same)):
+        assert torch.equal(got, want)
+    us = [bf16((M, N), 4).to(cuda), bf16((M, N + 256), 5).to(cuda)[:, :N]]
+    got = ops.gemm_sum(us, [w1, w3], trans_b=True)
+    assert rel_l2(f64(got), sum(f64(u) @ f64(w).T for u, w in zip(us, same))) <= RTOL2
+
+
 @pytest.mark.parametrize("M,N,K", JOINT)
 def test_gemm_swiglu_is_the_products_and_the_swiglu(cuda, M, N, K):
     # bit for bit the separate launches: same sums, same roundings

@@ -32,7 +32,8 @@ pytestmark = pytest.mark.gpu
 LAYER_RTOL = 2e-2
 
 
-def run_block(cuda, B, L, d, H, hidden, base, cu=None, doc_pos=False, seed=0):
+def run_block(cuda, B, L, d, H, hidden, base, cu=None, doc_pos=False, seed=0,
+              wide_w_3=0):
     from paper_2405_13226_amd.layer import OpenLMBlock
     log(f"block B={B} L={L} d={d} H={H} hidden={hidden} base={base} docs={cu is not None} doc_pos={doc_pos}")
     blk = OpenLMBlock(d, H, hidden, base, device=cuda, seed=seed,
@@ -42,6 +43,11 @@ def run_block(cuda, B, L, d, H, hidden, base, cu=None, doc_pos=False, seed=0):
             getattr(blk, n).add_(torch.randn(d, device=cuda).to(torch.bfloat16) * 0.2)
         for n in ("ln1_b", "ln2_b"):
             getattr(blk, n).add_(torch.randn(d, device=cuda).to(torch.bfloat16) * 0.2)
+    if wide_w_3:  # w_3 as the first columns of a wider matrix
+        wide = torch.zeros(d, hidden + wide_w_3, dtype=torch.bfloat16, device=cuda)
+        wide[:, :hidden] = blk.w_3.detach()
+        blk.w_3 = torch.nn.Parameter(wide[:, :hidden])
+        assert blk.w_3.stride() == (hidden + wide_w_3, 1)
     x0 = to_dev(synth.normal_bf16((B, L, d), seed, 21), cuda)
     dy = to_dev(synth.normal_bf16((B, L, d), seed, 22), cuda)
     w = {n: to_f64(p.detach()) for n, p in blk.weights().items()}
@@ -92,3 +98,9 @@ def test_block_parity_masked_chunk_document_positions(cuda):
     lens = synth.lognormal_doc_lengths(4, total_tokens=B * L, median=80, sigma=1.0)
     cu = dd.chunk_doclens(lens, B * L)
     run_block(cuda, B, L, 512, 4, 768, 10000.0, cu, True, seed=3)
+
+
+def test_block_parity_gate_weights_of_different_row_strides(cuda):
+    # the joint launches take one stride for both: these run as products of
+    # their own
+    run_block(cuda, 2, 256, 512, 4, 768, 10000.0, seed=5, wide_w_3=512)
