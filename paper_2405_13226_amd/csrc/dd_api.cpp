@@ -315,9 +315,7 @@ int run_gemm(dd::GemmArgs &a, int outs, size_t workspace_bytes)
             return DD_ERR_ALIGN;
     if (a.R && !aligned(a.R, 16))
         return DD_ERR_ALIGN;
-    const size_t need = a.kind == dd::GemmArgs::kPlain && a.segs == 1
-                            ? dd::gemm_workspace_bytes(M, N, K, a.groups)
-                            : 0;
+    const size_t need = a.may_split ? dd::gemm_workspace_bytes(M, N, K, a.groups) : 0;
     if (need && (!a.workspace || workspace_bytes < need))
         return DD_ERR_WORKSPACE;
     if (need && !aligned(a.workspace, 16))
@@ -371,7 +369,7 @@ int dd_gemm(const void *A, long long lda, int trans_a, const void *B, long long 
             size_t workspace_bytes, void *stream)
 {
     dd::GemmArgs a{dd::GemmArgs::kPlain, {A}, {B}, {C}, R, nullptr, nullptr, lda, ldb, ldc, 1, 1,
-                   M, N, K, trans_a != 0, trans_b != 0, workspace, stream};
+                   M, N, K, trans_a != 0, trans_b != 0, true, workspace, stream};
     return run_gemm(a, 1, workspace_bytes);
 }
 
@@ -384,7 +382,7 @@ int dd_gemm_group(const void *A, long long lda, int trans_a, const void *const *
     if (n < 1 || n > 3)
         return DD_ERR_SHAPE;
     dd::GemmArgs a{dd::GemmArgs::kPlain, {A}, {}, {}, nullptr, nullptr, nullptr, lda, ldb, ldc, n,
-                   1, M, N, K, trans_a != 0, trans_b != 0, workspace, stream};
+                   1, M, N, K, trans_a != 0, trans_b != 0, true, workspace, stream};
     for (int i = 0; i < n; ++i) {
         a.B[i] = B[i];
         a.C[i] = C[i];
@@ -400,7 +398,7 @@ int dd_gemm_sum(const void *const *A, long long lda, const void *const *B, long 
     if (n < 1 || n > 3)
         return DD_ERR_SHAPE;
     dd::GemmArgs a{dd::GemmArgs::kPlain, {}, {}, {C}, nullptr, nullptr, nullptr, lda, ldb, ldc, 1,
-                   n, M, N, K, false, trans_b != 0, nullptr, stream};
+                   n, M, N, K, false, trans_b != 0, false, nullptr, stream};
     for (int i = 0; i < n; ++i) {
         a.A[i] = A[i];
         a.B[i] = B[i];
@@ -412,7 +410,7 @@ int dd_gemm_swiglu(const void *X, long long ldx, const void *W1, const void *W3,
                    void *U, void *V, void *Y, long long ldy, int M, int N, int K, void *stream)
 {
     dd::GemmArgs a{dd::GemmArgs::kSwiglu, {X}, {W1, W3}, {U, V, Y}, nullptr, nullptr, nullptr,
-                   ldx, ldw, ldy, 1, 1, M, N, K, false, false, nullptr, stream};
+                   ldx, ldw, ldy, 1, 1, M, N, K, false, false, false, nullptr, stream};
     return run_gemm(a, 3, 0);
 }
 
@@ -423,7 +421,7 @@ int dd_gemm_swiglu_bwd(const void *dY, long long ldy, const void *W, long long l
     if (!U || !V)
         return DD_ERR_NULL;
     dd::GemmArgs a{dd::GemmArgs::kSwigluBackward, {dY}, {W}, {dU, dV}, nullptr, U, V, ldy, ldw,
-                   ldu, 1, 1, M, N, K, false, true, nullptr, stream};
+                   ldu, 1, 1, M, N, K, false, true, false, nullptr, stream};
     return run_gemm(a, 2, 0);
 }
 

@@ -841,8 +841,8 @@ int launch_gemm(const GemmArgs &a)
     // Columns of all groups (of both matrices for kEpiSwiglu).
     const bool swiglu = a.kind == GemmArgs::kSwiglu;
     const long long cols = static_cast<long long>(swiglu ? 2 : a.groups) * a.N;
-    const GemmPlan plan = gemm_plan(a.M, cols, static_cast<long long>(a.segs) * a.K,
-                                    a.kind == GemmArgs::kPlain && a.segs == 1);
+    const GemmPlan plan =
+        gemm_plan(a.M, cols, static_cast<long long>(a.segs) * a.K, a.may_split);
     const int splits = plan.splits;
     const int bm = plan.tile == GemmPlan::kSmall ? SmallTile::BM : GemmTile::BM;
     const int bn = plan.tile == GemmPlan::kLarge ? GemmTile::BN : SmallTile::BN;

@@ -80,6 +80,7 @@ struct GemmArgs {
     int groups, segs;         // at most 3, one of them 1
     int M, N, K;              // per group and segment
     bool trans_a, trans_b;    // A stored [K][M]; B stored [N][K] (not both)
+    bool may_split;           // the K axis of a kPlain product without segments
     void *workspace;          // fp32 [splits][groups][M][N] of gemm_plan, if it splits
     void *stream;
 };

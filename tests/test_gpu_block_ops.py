@@ -157,6 +157,16 @@ def test_joint_products_of_different_row_strides(cuda):
     assert rel_l2(f64(got), sum(f64(u) @ f64(w).T for u, w in zip(us, same))) <= RTOL2
 
 
+def test_gemm_sum_of_one_pair_takes_no_workspace(cuda):
+    # a reduction long enough that a plain product of these sizes is split
+    from paper_2405_13226_amd import lib
+    M, N, K = 512, 512, 16384
+    assert lib().dd_gemm_workspace_bytes(M, N, K) > 0
+    x, w = bf16((M, K), 1).to(cuda), bf16((N, K), 2).to(cuda)
+    got = ops.gemm_sum([x], [w], trans_b=True)
+    assert rel_l2(f64(got), f64(x) @ f64(w).T) <= RTOL
+
+
 @pytest.mark.parametrize("M,N,K", JOINT)
 def test_gemm_swiglu_is_the_products_and_the_swiglu(cuda, M, N, K):
     # bit for bit the separate launches: same sums, same roundings
