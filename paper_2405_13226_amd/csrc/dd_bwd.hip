@@ -32,6 +32,7 @@
 #include "dd_tile.hpp"
 #include "dd_launch.hpp"
 #include "dd_prof.hpp"
+#include "dd_routes.hpp"
 #include "dd_attn.h"
 
 namespace dd {
@@ -919,61 +920,6 @@ template __global__ void bwd_pair_kernel<128>(
 #undef DD_KV_ARGS
 #undef DD_Q_ARGS
 
-// Groups of waves over which a block's tiles are split.  The workgroups of a
-// small grid are all resident at once, so the heaviest causal block's chain of
-// L / 64 tiles is the launch's time, and the groups shorten it; dispatch (or
-// the persistent forms' walk, at L <= 2048) balances larger grids, and the
-// groups only cost them their final sum.
-//
-// dQ, measured whole backward, us with 1 / 2 / 4 groups, D = 64: 32 blocks of
-// L = 1000 51 / 44 / 44.5, 256 of L = 512 31.1 / 30.4 / 33.2, 480 of L = 300
-// 31.4 / 32.2 / 41.4, 512 of L = 1024 63.8 / 62.2 / 72.6, 768 of L = 1024 85 /
-// 91 / 106, 1024 of L = 2048 165 / 176 / 193; 256 of L = 8192 292 / 249 / 237,
-// 512 of L = 8192 320 / 297 / 287, 1024 of L = 4096 330 / 293 / 303, 2048 of
-// L = 8192 961 / 942 / 955.  D = 128: 384 of L = 3000 184 / 156, 564 of L =
-// 6000 438 / 400, 1024 of L = 8192 898 / 892, 256 of L = 1024 68.8 / 65.7, 256
-// of L = 256 31.5 / 33.5, 512 of L = 2048 183 / 185.5.
-template <int D>
-static int dq_key_groups(long long blocks, int L)
-{
-    const long long cus = device_cu_count();
-    if (D == 64)
-        return L > 2048 ? (blocks <= 2 * cus ? 4 : blocks <= 8 * cus ? 2 : 1)
-                        : (blocks <= 2 * cus ? 2 : 1);
-    return (L > 2048 && blocks <= 4 * cus) || (L > 768 && blocks <= cus) ? 2 : 1;
-}
-
-// dK/dV at D = 64, 1 / 2 groups: 64 blocks of L = 2048 81 / 70, 256 of L = 512
-// 31.1 / 28.8, 512 of L = 8192 320 / 280, 512 of L = 1024 63.8 / 68.7, 480 of
-// L = 300 31.4 / 36.2, 768 of L = 2048 135.7 / 135.4, 1024 of L = 8192 514 /
-// 522.  (At D = 128 the paired waves fill a CU's registers with one group.)
-static int dkdv_query_groups(long long blocks, int L)
-{
-    const long long cus = device_cu_count();
-    return blocks <= cus || (L > 2048 && blocks <= 3 * cus) ? 2 : 1;
-}
-
-// Whether dK/dV and dQ run as one launch (bwd_pair_kernel; blocks of each).
-// Its workgroups fill a CU, so it pays while both kernels' blocks fit the chip
-// about once; longer rows, whose heaviest blocks take longer than the average
-// ones, gain up to 5 blocks per 4 CUs.  Measured, one after the other / both
-// at once, us.  D = 64: 32 blocks of L = 256 18.4 / 11.5 (the one-kernel
-// backward), 128 of L = 512 25.0 / 16.4, 144 of L = 700 31 / 23, 192 of L =
-// 300 20.7 / 20.7, 256 of L = 1024 37.7 / 39.5, 64 of L = 2048 60 / 36, 256 of
-// L = 8192 196 / 146, 320 of L = 5000 140 / 122, 512 of L = 4096 153 / 158.
-// D = 128: 32 of L = 256 25.4 / 16.9, 128 of L = 1024 60 / 39, 192 of L = 512
-// 41.5 / 42.9, 320 of L = 5000 245 / 199, 512 of L = 4096 248 / 259.  At D =
-// 64 the one-kernel backward keeps rows of at most 128 tokens (128 blocks of
-// L = 64: 8.1 / 9.0).
-template <int D>
-static bool bwd_together(long long blocks, int L, bool rope)
-{
-    if (D == 64 && !rope && L <= 128)
-        return false;
-    const long long cus = device_cu_count();
-    return 8 * blocks <= 5 * cus || (L > 1024 && 4 * blocks <= 5 * cus);
-}
-
 // ---------------------------------------------------------------------------
 template <int D>
 static int launch_bwd_d(const BwdArgs &a)
@@ -995,7 +941,8 @@ static int launch_bwd_d(const BwdArgs &a)
     // Small grids: both kernels' blocks in one launch.
     const int nblk = (a.L + QTile<D>::BM - 1) / QTile<D>::BM;
     const long long blocks = static_cast<long long>(nblk) * a.B * a.H;
-    if (bwd_together<D>(blocks, a.L, s.rope != 0)) {
+    const long long cus = device_cu_count();
+    if (bwd_together(D, blocks, a.L, a.causal, s.rope != 0, cus)) {
         const int rows = a.B * a.L * a.H;
         const int kv_grid = static_cast<int>((blocks + kXcds - 1) / kXcds * kXcds);
         ProfScope prof(K_DKDV, st);
@@ -1027,7 +974,7 @@ static int launch_bwd_d(const BwdArgs &a)
             if (a.L <= kDqPersistMaxSpan)
                 pgrid = persistent_grid<dq_kernel<D, true, 1>>(256);
         const bool persist = pgrid > 0 && pgrid < all;
-        const int ks = dq_key_groups<D>(static_cast<long long>(nqb) * a.B * a.H, a.L);
+        const int ks = dq_key_groups(D, blocks, a.L, a.causal, a.cu != nullptr, cus);
         auto kern = ks == 2 ? dq_kernel<D, false, 2> : dq_kernel<D, false, 1>;
         if constexpr (D == 64) {
             if (ks == 4)
@@ -1059,7 +1006,7 @@ static int launch_bwd_d(const BwdArgs &a)
                                         ? persistent_grid<dkdv1_kernel<D, true, 1>>(64 * T::NW)
                                         : 0;
             const bool persist = pgrid > 0 && pgrid < all;
-            const int ks = dkdv_query_groups(n_items, a.L);
+            const int ks = dkdv_query_groups(n_items, a.L, a.causal, a.cu != nullptr, cus);
             auto kern = ks == 2   ? dkdv1_kernel<D, false, 2>
                         : persist ? dkdv1_kernel<D, true, 1>
                                   : dkdv1_kernel<D, false, 1>;

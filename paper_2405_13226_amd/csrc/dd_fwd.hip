@@ -23,6 +23,7 @@
 #include "dd_launch.hpp"
 #include "dd_prof.hpp"
 #include "dd_rope.hpp"
+#include "dd_routes.hpp"
 #include "dd_attn.h"
 
 #include <algorithm>
@@ -490,31 +491,6 @@ template __global__ void fwd_kernel<64, false, true, 4>(DD_FWD_ARGS);
 template __global__ void fwd_kernel<128, false, true, 2>(DD_FWD_ARGS);
 #undef DD_FWD_ARGS
 
-// Groups of waves over which a query block's keys are split.  All of a small
-// grid's workgroups are resident at once (four per CU at D = 64, two at 128),
-// so nothing balances the causal blocks: the heaviest, with L / 64 key tiles,
-// is the launch's time, and the groups shorten it.  A larger grid is balanced
-// by dispatch, and the groups only cost it their final sum (and at D = 128,
-// where two groups fill a CU, its second workgroup).  Measured, causal, us
-// with 1 / 2 / 4 groups; D = 64: 64 blocks of L = 2048 32 / 24 / 22, 256 of
-// L = 8192 114 / 81 / 70, 256 of L = 512 12.7 / 10.9 / 11.9, 512 of L = 8192
-// 118 / 97 / 90, 480 of L = 300 13.1 / 13.3 / 19.8, 1024 of L = 4096 134 / 103
-// / 106, 1280 of L = 5000 175 / 152 / 158, 768 of L = 1024 34.9 / 35.8 / 42.7,
-// 1536 of L = 8192 255 / 257 / 266.  D = 128: 128 of L = 4096 80 / 62, 512 of
-// L = 4096 117 / 89, 640 of L = 2500 88.5 / 86.2, 1024 of L = 8192 278 / 290,
-// 256 of L = 256 12.4 / 12.7, 384 of L = 1024 35.8 / 35.3, 512 of L = 1024
-// 37 / 42, 512 of L = 2048 65.2 / 66.0.
-template <int D>
-static int fwd_key_groups(long long blocks, int L)
-{
-    const long long cus = device_cu_count();
-    if (D == 64)
-        return blocks <= cus && L > 768                          ? 4
-               : blocks <= 2 * cus || (L > 1024 && blocks <= 5 * cus) ? 2
-                                                                      : 1;
-    return blocks <= cus || (L > 2048 && 2 * blocks <= 5 * cus) ? 2 : 1;
-}
-
 template <int D, bool ROPE>
 static int launch_fwd_d(const FwdArgs &a)
 {
@@ -528,7 +504,8 @@ static int launch_fwd_d(const FwdArgs &a)
     const long long pgrid =
         a.L <= kFwdPersistMaxSpan<D> ? persistent_grid<fwd_kernel<D, true, ROPE, 1>>(256) : 0;
     const bool persist = pgrid > 0 && pgrid < all;
-    const int ks = fwd_key_groups<D>(static_cast<long long>(nqb) * a.B * a.H, a.L);
+    const int ks = fwd_key_groups(D, static_cast<long long>(nqb) * a.B * a.H, a.L, a.causal,
+                                  a.cu != nullptr, device_cu_count());
     auto kern = persist ? fwd_kernel<D, true, ROPE, 1> : fwd_kernel<D, false, ROPE, 1>;
     if (ks == 2)
         kern = fwd_kernel<D, false, ROPE, 2>;
