@@ -374,9 +374,8 @@ gemm_kernel(GemmOperands op, GemmSizes sz)
 #pragma unroll
             for (int j = 0; j < 2; ++j)
                 acc[x >> 1][x & 1][i][j] = f32x4{};
-    auto products = [&](f32x4 (&c)[4][2], const bf16x8 (&a)[4][2],
+    auto multiply = [&](f32x4 (&c)[4][2], const bf16x8 (&a)[4][2],
                         const bf16x8 (&b)[2][2]) __attribute__((always_inline)) {
-        __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
@@ -384,6 +383,11 @@ gemm_kernel(GemmOperands op, GemmSizes sz)
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
                     c[i][j] = mfma16(b[j][kk], a[i][kk], c[i][j]);  // rows n, columns m
+    };
+    auto products = [&](f32x4 (&c)[4][2], const bf16x8 (&a)[4][2],
+                        const bf16x8 (&b)[2][2]) __attribute__((always_inline)) {
+        __builtin_amdgcn_s_setprio(1);
+        multiply(c, a, b);
         __builtin_amdgcn_s_setprio(0);
         plain_barrier();
     };
@@ -417,43 +421,55 @@ gemm_kernel(GemmOperands op, GemmSizes sz)
         products(acc[1][0], a1, b0);
     };
 
-    // The loop takes K steps in pairs; an odd count starts with a step of
-    // zeros in stage 0.
-    if (nkt & 1) {
-#pragma unroll
-        for (int x = 0; x < 8; ++x)
-            *reinterpret_cast<u32x4 *>(lds + (x >> 2) * T::SIDE + ((x >> 1) & 1) * 2 * T::HALF +
-                                       (x & 1) * T::SUB + tid * 8) = u32x4{};
-    } else {
-        load_a(0, 0);
-        load_b(0, 0);
-        load_b(1, 0);
-        load_a(1, 0);
+    // The loop takes K steps in pairs, stage 0 first; an odd count starts with
+    // a step of its own in stage 1.
+    auto load_step = [&](int S) __attribute__((always_inline)) {
+        load_a(0, S);
+        load_b(0, S);
+        load_b(1, S);
+        load_a(1, S);
         at.next(ka, kb);
+    };
+    if (nkt == 1) {
+        // Nothing to overlap: one wait for the step's tiles, no phases.  5632 x
+        // 3072, us, with one barrier per step / in four phases / here: 15.4 /
+        // 16.6 / 15.1.  (Two steps, 18.7 / 19.1, lose 2-4% for A B^T only and
+        // gained nothing without the phases.)
+        load_step(0);
+        wait_and_barrier<0>();
+        read_a(a0, 0, 0);
+        read_b(b0, 0, 0);
+        multiply(acc[0][0], a0, b0);
+        read_b(b1, 1, 0);
+        multiply(acc[0][1], a0, b1);
+        read_a(a1, 1, 0);
+        multiply(acc[1][1], a1, b1);
+        multiply(acc[1][0], a1, b0);
+    } else {
+        const int s0 = nkt & 1;
+        load_step(s0);
+        load_step(1 - s0);
+        wait_and_barrier<8>();
+        read_a(a0, 0, s0);
+        // Phase 1 refills the half just read: as in the loop, only after a
+        // barrier that every wave reaches with its reads returned (a load of
+        // one wave writes rows that all the others read).
+        wait_and_barrier<8>();
+        // The second group of four waves runs half a phase behind the first:
+        // on every SIMD one wave issues products while the other reads and
+        // loads.
+        if (wm == 1)
+            plain_barrier();
+        for (int kt = 2 - s0; kt < nkt; kt += 2) {
+            if (kt > 1)
+                step(IC<0>{}, IC<0>{});
+            step(IC<1>{}, IC<0>{});
+        }
+        step(IC<0>{}, IC<1>{});
+        step(IC<1>{}, IC<2>{});
+        if (wm == 0)
+            plain_barrier();
     }
-    load_a(0, 1);
-    load_b(0, 1);
-    load_b(1, 1);
-    load_a(1, 1);
-    at.next(ka, kb);
-    wait_and_barrier<8>();
-    read_a(a0, 0, 0);
-    // Phase 1 refills the half just read: as in the loop, only after a barrier
-    // that every wave reaches with its reads returned (a load of one wave
-    // writes rows that all the others read).
-    wait_and_barrier<8>();
-    // The second group of four waves runs half a phase behind the first: on
-    // every SIMD one wave issues products while the other reads and loads.
-    if (wm == 1)
-        plain_barrier();
-    for (int kt = 2; kt < nkt; kt += 2) {
-        step(IC<0>{}, IC<0>{});
-        step(IC<1>{}, IC<0>{});
-    }
-    step(IC<0>{}, IC<1>{});
-    step(IC<1>{}, IC<2>{});
-    if (wm == 0)
-        plain_barrier();
 
     // Accumulator (ha, hb, i, j), register e: row m = 128 ha + 64 wm + 16 i +
     // l16, column n = 128 hb + 32 wn + 16 j + 4 g + e of the tile.

@@ -114,3 +114,15 @@ def test_large_gemm_first_refill_waits_for_the_reads(tmp_path):
         ordered = any(a.startswith("s_waitcnt") and "lgkmcnt(0)" in a and b.startswith("s_barrier")
                       for a, b in zip(lines[first:load], lines[first + 1:load]))
         assert ordered, sym
+
+
+def test_large_gemm_takes_a_single_step_without_phases(tmp_path):
+    # K = 64 is one step: its 64 products run without a barrier in between
+    # (a phase of the pipelined loop is 16).
+    asm = device_asm("dd_gemm.hip", tmp_path)
+    for sym in sorted(set(re.findall(r"^(_ZN2dd11gemm_kernelI\w+):", asm, re.M))):
+        longest = run = 0
+        for ln in kernel_body(asm, sym)[1]:
+            run = 0 if ln.startswith("s_barrier") else run + ln.startswith("v_mfma")
+            longest = max(longest, run)
+        assert longest >= 64, (sym, longest)
