@@ -37,13 +37,25 @@ __device__ __forceinline__ float wave_sum(float v)
 
 constexpr int kLnWaves = 4;       // waves (rows in flight) per workgroup
 
-// Rows per workgroup of the backward: few enough that every CU has four
-// workgroups (a row is a chain of loads, two reductions and a store: 2048
-// rows of 1024 took 26.5 us at 64 rows, 6.7 at 8), but each has 8 or
-// more, since every workgroup writes a row of column partials.
-__host__ __device__ constexpr int ln_rows_per_wg(int rows)
+// Rows per workgroup of the backward.  Few, because a row is a chain of loads,
+// two reductions and a store; but every workgroup writes a row of column
+// partials, and at most kLnOneStage of those are summed in one launch.  So one
+// workgroup per CU of an MI355X while that leaves it a few dozen rows (8 at
+// least), then two, of at most 64 rows; and four (1024) where those would be
+// more than the 4, 3, 2 per CU that are resident at d = 512, 1024, 2048.  us
+// with 64 rows per workgroup / 8 and later 4 per CU / this rule: 4096 x 1024
+// 22.3 / 12.2 / 10.5, 8192 x 2048 33.4 / 28.5 / 22.7, 16,384 x 2048 38.8 /
+// 42.2 / 36.4, 32,768 x 1024 37.4 / 39.6 / 37.6, 45,000 x 1024 52.2 / 58.1 /
+// 51.8, 33,000 x 2048 110.6 / 91.2 / 91.2.
+constexpr int kLnOneStage = 256;
+
+__host__ __device__ constexpr int ln_rows_per_wg(int rows, int d)
 {
-    return rows >= 65536 ? 64 : rows <= 8192 ? 8 : (rows + 4095) / 4096 * 4;
+    const int one = d == 512 ? 8192 : d == 1024 ? 12288 : 16384;
+    const int two = d == 512 ? 65536 : d == 1024 ? 49152 : 32768;
+    const int wgs = (rows <= one ? 1 : rows <= two ? 2 : 4) * kLnOneStage;
+    const int per = static_cast<int>((rows + wgs - 1LL) / wgs + 3) / 4 * 4;
+    return per < 8 ? 8 : per > 64 ? 64 : per;
 }
 
 // CH = d / 512 chunks of 8 elements per lane.
@@ -117,7 +129,7 @@ layernorm_bwd_kernel(const uint16_t *__restrict__ X, const uint16_t *__restrict_
         for (int i = 0; i < 8; ++i)
             dw[c][i] = db[c][i] = 0.f;
     }
-    const int per_wg = ln_rows_per_wg(rows);
+    const int per_wg = ln_rows_per_wg(rows, CH * 512);
     const int row0 = static_cast<int>(blockIdx.x) * per_wg;
     for (int rr = wave; rr < per_wg; rr += kLnWaves) {
         const int row = row0 + rr;
@@ -230,11 +242,9 @@ layernorm_param_grad_kernel(const float *__restrict__ sums, int d, uint16_t *__r
     *dst = __builtin_bit_cast(uint16_t, v);
 }
 
-// The same in one launch for at most kLnOneStage partial rows (2048 rows of
-// input): 16 waves sum 64 columns, wave w the rows w, w + 16, ....  The two
-// launches took 3.8 + 3.7 us there, mostly their own latency; this one 4.1.
-constexpr int kLnOneStage = 256;
-
+// The same in one launch for at most kLnOneStage partial rows: 16 waves sum 64
+// columns, wave w the rows w, w + 16, ....  The two launches took 3.8 + 3.7 us
+// at 256 rows, mostly their own latency; this one 4.1.
 __global__ void __launch_bounds__(1024)
 layernorm_param_one_kernel(const float *__restrict__ part, int nparts, int d,
                            uint16_t *__restrict__ dW, uint16_t *__restrict__ dB)
@@ -315,10 +325,11 @@ template __global__ void layernorm_bwd_kernel<4>(DD_LNB_ARGS);
 
 size_t layernorm_workspace_bytes(int rows, int d)
 {
-    // The workgroups' partial rows, then the chunk sums.
-    // (At most 1024 of them below 65,536 rows; the bound grows with the rows,
-    // so that scratch for the longest input serves every shorter one.)
-    const long long nparts = rows >= 65536 ? (rows + 63LL) / 64 : std::min((rows + 7) / 8, 1024);
+    // The workgroups' partial rows, then the chunk sums.  (At most four per CU
+    // below 65,536 rows; the bound grows with the rows, so that scratch for the
+    // longest input serves every shorter one.)
+    const long long nparts =
+        std::max((rows + 63LL) / 64, std::min((rows + 7LL) / 8, 4LL * kLnOneStage));
     return static_cast<size_t>(nparts + kLnChunks) * 2 * d * sizeof(float);
 }
 
@@ -342,7 +353,7 @@ int launch_layernorm_fwd(const LayerNormArgs &a)
 int launch_layernorm_bwd(const LayerNormArgs &a)
 {
     hipStream_t st = static_cast<hipStream_t>(a.stream);
-    const int per_wg = ln_rows_per_wg(a.rows), nparts = (a.rows + per_wg - 1) / per_wg;
+    const int per_wg = ln_rows_per_wg(a.rows, a.d), nparts = (a.rows + per_wg - 1) / per_wg;
     const dim3 grid(static_cast<unsigned>(nparts)), block(64 * kLnWaves);
     const auto *X = static_cast<const uint16_t *>(a.X);
     const auto *W = static_cast<const uint16_t *>(a.w);

@@ -191,8 +191,10 @@ def ln_ref(x, w, b, dy, dres, eps=1e-5):
     return y, dx, (dy * xh).sum(0), dy.sum(0), mu[:, 0], rstd[:, 0]
 
 
+# (edges of the backward's rows per workgroup and of its one-launch column sums)
 @pytest.mark.parametrize("rows,d", [(1, 512), (100, 512), (777, 1024), (2048, 1024), (2049, 1024),
-                                    (4096, 2048)])
+                                    (4096, 2048), (8192, 512), (8193, 512), (16384, 2048),
+                                    (16385, 2048), (32769, 2048)])
 def test_layer_norm(cuda, rows, d):
     x = bf16((rows, d), rows, 2.0) + 0.5
     w, b = bf16((d,), 5) * 0.3 + 1, bf16((d,), 6) * 0.3
