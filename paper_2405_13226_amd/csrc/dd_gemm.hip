@@ -54,10 +54,10 @@
 #include "dd_tile.hpp"
 #include "dd_internal.h"
 #include "dd_launch.hpp"
+#include "dd_routes.hpp"
 #include "dd_attn.h"
 
 #include <algorithm>
-#include <cmath>
 
 namespace dd {
 
@@ -778,49 +778,9 @@ DD_GEMM_INST(false, false, kEpiSwiglu);
 DD_GEMM_INST(false, true, kEpiSwigluBwd);
 #undef DD_GEMM_INST
 
-// Estimated time (us) of `tiles` tiles with `splits` K parts: rounds of
-// workgroups over the CUs (one per CU), each a start-up and tail plus its K
-// steps, then the partial sums' write and read.  The constants are fits to
-// graph-replayed products.  One round of large, tall and small tiles: 2048 x
-// 1024 at K = 1024 takes 21 / 15-17 / 12.5-13 us, at K = 5632 88 / 58 / 42-47
-// (with two splits 59 / 44 / 40); 2048 x 2816 at K = 1024 (88, 176 and 352
-// workgroups) 23 / 17 / 23.  A full chip runs slower, large tiles for their
-// power: 8192 x 2048 at K = 2048 (256, 512, 1024 workgroups) 54 / 69 / 86.
-static double gemm_cost(double tiles, double cus, double steps, double splits, double mn,
-                        int tile)
+static GemmPlan plan_on_device(int M, long long N, long long K, bool may_split)
 {
-    const double wgs = tiles * splits, rounds = std::ceil(wgs / cus);
-    const double part = std::min(wgs / cus, 1.0);  // CUs in use
-    const double step = tile == GemmPlan::kSmall  ? (part < 1 ? 0.42 : 0.55)
-                        : tile == GemmPlan::kTall ? (part < 1 ? 0.60 + 0.15 * part : 0.95)
-                                                  : (part < 1 ? 1.02 + 0.2 * part : 1.4);
-    const double reduce = splits > 1 ? 6.0 + splits * mn * 8.0 / 4.0e6 : 0.0;
-    return rounds * (std::ceil(steps / splits) * step + 6.0) + reduce;
-}
-
-// The cheapest tile and number of K splits (1, 2, 4, ...) for a product of
-// M x N (all groups' columns together) over K.  Splits are multiples of 64
-// and at least 1024 long, and more of them than two large tiles per CU are
-// never needed.
-GemmPlan gemm_plan(int M, long long N, long long K, bool may_split)
-{
-    const int cus = std::max(device_cu_count(), 1);
-    const long long tiles = static_cast<long long>(M / GemmTile::BM) * (N / GemmTile::BN);
-    GemmPlan best{GemmPlan::kLarge, 1};
-    double cost = -1;
-    for (int s = 1;; s *= 2) {
-        for (const GemmPlan::Tile tile : {GemmPlan::kLarge, GemmPlan::kTall, GemmPlan::kSmall}) {
-            const double c = gemm_cost(static_cast<double>(tiles << tile), cus, K / 64.0, s,
-                                       static_cast<double>(M) * N, tile);
-            if (cost < 0 || c < cost) {
-                cost = c;
-                best = GemmPlan{tile, s};
-            }
-        }
-        if (!may_split || tiles * s >= 2LL * cus || K / (2 * s) < 1024 ||
-            (K / (2 * s)) % GemmTile::BK != 0)
-            return best;
-    }
+    return gemm_plan(M, N, K, may_split, device_cu_count());
 }
 
 // xm of tile_of: the one whose groups of 32 tiles read the fewest panels per
@@ -847,7 +807,7 @@ static int tile_rows_step(int tiles_m, int tiles_n)
 
 size_t gemm_workspace_bytes(int M, int N, int K, int groups)
 {
-    const GemmPlan p = gemm_plan(M, static_cast<long long>(groups) * N, K, true);
+    const GemmPlan p = plan_on_device(M, static_cast<long long>(groups) * N, K, true);
     return p.splits > 1 ? static_cast<size_t>(p.splits) * groups * M * N * sizeof(float) : 0;
 }
 
@@ -858,7 +818,7 @@ int launch_gemm(const GemmArgs &a)
     const bool swiglu = a.kind == GemmArgs::kSwiglu;
     const long long cols = static_cast<long long>(swiglu ? 2 : a.groups) * a.N;
     const GemmPlan plan =
-        gemm_plan(a.M, cols, static_cast<long long>(a.segs) * a.K, a.may_split);
+        plan_on_device(a.M, cols, static_cast<long long>(a.segs) * a.K, a.may_split);
     const int splits = plan.splits;
     const int bm = plan.tile == GemmPlan::kSmall ? SmallTile::BM : GemmTile::BM;
     const int bn = plan.tile == GemmPlan::kLarge ? GemmTile::BN : SmallTile::BN;

@@ -84,14 +84,6 @@ struct GemmArgs {
     void *workspace;          // fp32 [splits][groups][M][N] of gemm_plan, if it splits
     void *stream;
 };
-// How a product of these sizes runs: on tiles of 256 x 256, 256 x 128 or
-// 128 x 128 (the value is log2 of the tiles per 256 x 256), with the K axis in
-// `splits` parts (1: none; more need the workspace).
-struct GemmPlan {
-    enum Tile { kLarge, kTall, kSmall } tile;
-    int splits;
-};
-GemmPlan gemm_plan(int M, long long N, long long K, bool may_split);
 size_t gemm_workspace_bytes(int M, int N, int K, int groups);
 int launch_gemm(const GemmArgs &a);
 

@@ -1,21 +1,25 @@
-// dd_routes.hpp -- which kernel form an attention call takes, by the number of
-// its 128-row blocks, the row length L, the mask and the number of CUs.  Plain
-// C++, so that a host program can ask where a shape goes.
+// dd_routes.hpp -- which kernel form a call takes: an attention call by the
+// number of its 128-row blocks, the row length L, the mask and the number of
+// CUs, a product by its sizes.  Plain C++, so that a host program can ask where
+// a shape goes.
 //
-// Groups of waves share a block's tiles.  The workgroups of a small grid are
-// all resident at once, so the heaviest block's chain of tiles is the launch's
-// time, and the groups shorten it.  A larger grid is balanced by dispatch (or
+// Attention: groups of waves share a block's tiles.  The workgroups of a small
+// grid are all resident at once, so the heaviest block's chain of tiles is the
+// launch's time, and the groups shorten it.  A larger grid is balanced by dispatch (or
 // by the persistent forms' walk), and the groups cost it their final sum and
 // their share of a CU.  That balance is what the causal mask makes uneven and
 // documents more so: without the causal mask every block has the same work, a
 // grid that covers the CUs gains nothing, and the groups stop at one block per
 // CU or two.
 //
-// The figures below are graph-replayed times with two (or four) groups over
+// The figures of the attention rules are graph-replayed times with two (or four) groups over
 // those with one, per row length and blocks, causal / not causal / causal with
 // documents (log-normal lengths, median 600); a rule takes the groups where
 // they gain.
 #pragma once
+
+#include <algorithm>
+#include <cmath>
 
 namespace dd {
 
@@ -112,6 +116,59 @@ inline bool bwd_together(int D, long long blocks, int L, bool causal, bool rope,
     return 2 * blocks <= cus || (causal && L > 256 && 16 * blocks <= 9 * cus) ||
            (L > 512 && 8 * blocks <= 5 * cus) ||
            (L > (causal ? 1024 : 2048) && 4 * blocks <= 5 * cus);
+}
+
+// How a product of these sizes runs: on tiles of 256 x 256, 256 x 128 or
+// 128 x 128 (the value is log2 of the tiles per 256 x 256), with the K axis in
+// `splits` parts (1: none; more need the workspace).
+struct GemmPlan {
+    enum Tile { kLarge, kTall, kSmall } tile;
+    int splits;
+};
+
+// Estimated time (us) of `tiles` tiles with `splits` K parts: rounds of
+// workgroups over the CUs (one per CU), each a start-up and tail plus its K
+// steps, then the partial sums' write and read.  The constants are fits to
+// graph-replayed products.  One round of large, tall and small tiles: 2048 x
+// 1024 at K = 1024 takes 21 / 15-17 / 12.5-13 us, at K = 5632 88 / 58 / 42-47
+// (with two splits 59 / 44 / 40); 2048 x 2816 at K = 1024 (88, 176 and 352
+// workgroups) 23 / 17 / 23.  A full chip runs slower, large tiles for their
+// power: 8192 x 2048 at K = 2048 (256, 512, 1024 workgroups) 54 / 69 / 86.
+inline double gemm_cost(double tiles, double cus, double steps, double splits, double mn,
+                        int tile)
+{
+    const double wgs = tiles * splits, rounds = std::ceil(wgs / cus);
+    const double part = std::min(wgs / cus, 1.0);  // CUs in use
+    const double step = tile == GemmPlan::kSmall  ? (part < 1 ? 0.42 : 0.55)
+                        : tile == GemmPlan::kTall ? (part < 1 ? 0.60 + 0.15 * part : 0.95)
+                                                  : (part < 1 ? 1.02 + 0.2 * part : 1.4);
+    const double reduce = splits > 1 ? 6.0 + splits * mn * 8.0 / 4.0e6 : 0.0;
+    return rounds * (std::ceil(steps / splits) * step + 6.0) + reduce;
+}
+
+// The cheapest tile and number of K splits (1, 2, 4, ...) for a product of
+// M x N (all groups' columns together) over K.  Splits are multiples of 64
+// and at least 1024 long, and more of them than two large tiles per CU are
+// never needed.
+inline GemmPlan gemm_plan(int M, long long N, long long K, bool may_split, int cus)
+{
+    cus = std::max(cus, 1);
+    const long long tiles = static_cast<long long>(M / 256) * (N / 256);
+    GemmPlan best{GemmPlan::kLarge, 1};
+    double cost = -1;
+    for (int s = 1;; s *= 2) {
+        for (const GemmPlan::Tile tile : {GemmPlan::kLarge, GemmPlan::kTall, GemmPlan::kSmall}) {
+            const double c = gemm_cost(static_cast<double>(tiles << tile), cus, K / 64.0, s,
+                                       static_cast<double>(M) * N, tile);
+            if (cost < 0 || c < cost) {
+                cost = c;
+                best = GemmPlan{tile, s};
+            }
+        }
+        if (!may_split || tiles * s >= 2LL * cus || K / (2 * s) < 1024 ||
+            (K / (2 * s)) % 64 != 0)
+            return best;
+    }
 }
 
 }  // namespace dd

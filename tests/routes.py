@@ -1,4 +1,4 @@
-"""The kernel forms that an attention call takes (csrc/dd_routes.hpp, compiled
+"""The kernel forms that a call takes (csrc/dd_routes.hpp, compiled
 by the host compiler), so that tests can say which one they mean to reach."""
 import ctypes
 import functools
@@ -16,6 +16,10 @@ int fwd(int D, long long n, int L, int c, int d, int cus) { return dd::fwd_key_g
 int dq(int D, long long n, int L, int c, int d, int cus) { return dd::dq_key_groups(D, n, L, c, d, cus); }
 int kv(long long n, int L, int c, int d, int cus) { return dd::dkdv_query_groups(n, L, c, d, cus); }
 int both(int D, long long n, int L, int c, int r, int cus) { return dd::bwd_together(D, n, L, c, r, cus); }
+int gemm(int M, long long N, long long K, int split, int cus) {
+    const dd::GemmPlan p = dd::gemm_plan(M, N, K, split, cus);
+    return 1000 * p.tile + p.splits;
+}
 }
 """
 
@@ -32,6 +36,7 @@ def _lib():
     h.fwd.argtypes = h.dq.argtypes = [ctypes.c_int, n] + [ctypes.c_int] * 4
     h.both.argtypes = [ctypes.c_int, n] + [ctypes.c_int] * 4
     h.kv.argtypes = [n] + [ctypes.c_int] * 4
+    h.gemm.argtypes = [ctypes.c_int, n, n] + [ctypes.c_int] * 2
     return h
 
 
@@ -53,3 +58,9 @@ def backward(B, L, H, D, causal=True, docs=False, rope=False):
         return "short"
     return (_lib().dq(D, n, L, causal, docs, CUS),
             _lib().kv(n, L, causal, docs, CUS) if D == 64 else 1)
+
+
+def gemm(M, N, K, split=True):
+    """(tile, K splits) of a product; N is the columns of all groups."""
+    v = _lib().gemm(M, N, K, split, CUS)
+    return ("large", "tall", "small")[v // 1000], v % 1000

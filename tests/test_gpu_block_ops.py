@@ -15,6 +15,7 @@ import torch
 
 from paper_2405_13226_amd import block_ops as ops
 
+import routes
 from parity import log, rel_l2
 
 pytestmark = pytest.mark.gpu
@@ -38,6 +39,8 @@ def f64(t):
     (10240, 2816, 128, 0, 0), (10240, 2816, 128, 0, 1),
     (65536, 2048, 2048, 0, 0),    # the block's output projection at 65,536 tokens
     (2048, 2048, 65536, 1, 0),    # its weight gradient
+    (1024, 2048, 16384, 1, 0),    # tall tiles, K split
+    (1024, 2048, 16384, 0, 0), (1024, 2048, 16384, 0, 1),
 ])
 def test_gemm(cuda, M, N, K, ta, tb):
     log(f"gemm M={M} N={N} K={K} ta={ta} tb={tb}")
@@ -71,12 +74,15 @@ def test_gemm_short_reductions(cuda, M, N, K, ta, tb):
     assert rel_l2(f64(c), ref) <= RTOL
 
 
-@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
-def test_gemm_wide_row_strides(cuda, ta, tb):
+@pytest.mark.parametrize("M,N,K,ta,tb,tile", [
+    (256, 256, 64, 0, 0, "small"), (256, 256, 64, 0, 1, "small"), (256, 256, 64, 1, 0, "small"),
+    (2048, 2816, 64, 0, 0, "tall"), (2048, 2816, 64, 1, 0, "tall"),
+    (2048, 8192, 64, 0, 0, "large"), (2048, 8192, 64, 1, 0, "large")])
+def test_gemm_wide_row_strides(cuda, M, N, K, ta, tb, tile):
     # Row strides from which eight rows no longer fit 32-bit byte offsets, on
     # the operand with 64 rows (34 GB, of which 64 rows are used); A B^T has
-    # none with so few, its A is 2^25 elements a row (17 GB).
-    M, N, K = 256, 256, 64
+    # none with so few, its A is 2^25 elements a row (17 GB), short of them.
+    assert routes.gemm(M, N, K) == (tile, 1)
     ld = (1 << (25 if tb else 28)) + 8
     a = bf16((K, M) if ta else (M, K), 1)
     b = bf16((N, K) if tb else (K, N), 2)
@@ -115,7 +121,8 @@ JOINT = [(256, 256, 64), (512, 768, 192), (2304, 2816, 128), (2048, 1536, 320), 
 
 
 @pytest.mark.parametrize("n", [2, 3])
-@pytest.mark.parametrize("M,N,K", JOINT + [(512, 512, 8192)])  # the last splits K
+# the last two split K, on small and (two groups) tall tiles
+@pytest.mark.parametrize("M,N,K", JOINT + [(512, 512, 8192), (1024, 1024, 16384)])
 def test_gemm_group(cuda, M, N, K, n):
     # both uses: columns of one weight matrix, and weight gradients written
     # into columns of one matrix
@@ -155,6 +162,17 @@ def test_joint_products_of_different_row_strides(cuda):
     us = [bf16((M, N), 4).to(cuda), bf16((M, N + 256), 5).to(cuda)[:, :N]]
     got = ops.gemm_sum(us, [w1, w3], trans_b=True)
     assert rel_l2(f64(got), sum(f64(u) @ f64(w).T for u, w in zip(us, same))) <= RTOL2
+
+
+def test_the_tests_sizes_reach_every_tile():
+    short = [(256, 512), (2048, 2816), (2048, 8192)]
+    assert [routes.gemm(m, n, 64)[0] for m, n in short] == ["small", "tall", "large"]
+    assert routes.gemm(1024, 512, 8192) == ("small", 8)
+    assert routes.gemm(2048, 2048, 65536) == ("large", 4)
+    assert routes.gemm(1024, 2048, 16384) == ("tall", 4)
+    assert routes.gemm(512, 2 * 512, 8192)[1] > 1
+    tiles = {routes.gemm(m, f * n, s * k, False)[0] for m, n, k in JOINT for f, s in ((2, 1), (1, 2))}
+    assert tiles == {"small", "tall", "large"}
 
 
 def test_gemm_sum_of_one_pair_takes_no_workspace(cuda):
