@@ -4,14 +4,16 @@ The library allocates nothing, synchronises nothing and issues no memset on
 the caller's stream, so a forward + backward can be captured once and
 replayed.  Each replay is checked bit for bit against the eager result, with
 eager work of the program itself and a device synchronisation between the
-replays.  Rows of 700 tokens take the persistent kernels (several work items
-per workgroup), rows of 200 tokens at D=64 the one-kernel backward; the
-document-masked cases pass offsets prepared outside the capture (their
+replays.  Four slices take the forms of small grids (wave groups in the
+forward, the joint backward); 144 slices of 700 tokens the persistent kernels
+(several work items per workgroup) and dQ and dK/dV as launches of their own,
+144 of 200 tokens at D=64 the one-kernel backward.  The document-masked cases pass offsets prepared outside the capture (their
 host-to-device copy is not a graph operation).
 """
 import pytest
 import torch
 
+import routes
 import synth
 import paper_2405_13226_amd as dd
 from paper_2405_13226_amd.attention import DocLens
@@ -21,14 +23,19 @@ from parity import log, to_dev
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("B", [2, 72])
 @pytest.mark.parametrize("D,docs,L", [(64, False, 700), (128, False, 700), (64, True, 700),
                                       (128, True, 700), (64, False, 200), (64, True, 200)])
-def test_graph_replay_matches_eager(cuda, D, docs, L):
-    B, H = 2, 2
+def test_graph_replay_matches_eager(cuda, D, docs, L, B):
+    H = 2
+    want = "joint" if B == 2 else (1, 1) if L == 700 else "short"
+    assert routes.backward(B, L, H, D, True, docs) == want
+    assert L == 200 or (routes.forward(B, L, H, D, True, docs) > 1) == (B == 2)
     x = {n: to_dev(a, cuda) for n, a in synth.attention_inputs(B, L, H, D, seed=40 + D).items()}
     offs = [0, 150, 600, 700, 1100, 1400] if L == 700 else [0, 30, 170, 200, 290, 400]
+    offs = [o + i * 2 * L for i in range(B // 2) for o in offs[:-1]] + [B * L]
     cu = DocLens(offs, B * L, cuda) if docs else None
-    log(f"graph case D={D} docs={docs} L={L}")
+    log(f"graph case B={B} D={D} docs={docs} L={L}")
 
     def step():
         o, lse = dd.forward(x["q"], x["k"], x["v"], cu_doclens=cu)

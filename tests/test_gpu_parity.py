@@ -7,6 +7,7 @@ pairs are independent.  Tolerances are in tests/parity.py.
 import numpy as np
 import pytest
 
+import routes
 import synth
 from paper_2405_13226_amd import dd
 
@@ -55,12 +56,19 @@ def test_small_grids(cuda, L, D, mode):
 
 
 # Grids past the joint launch's range whose blocks are still split: dQ over two
-# groups (and four, D = 64 from L = 2049 on), dK/dV at D = 64 over two.
-@pytest.mark.parametrize("L,H,D", [(700, 32, 64), (1153, 40, 64), (2177, 20, 64), (900, 24, 128),
-                                   (2177, 20, 128)])
-def test_grids_of_split_blocks(cuda, L, H, D):
-    check_case(1, L, H, D, causal=True, seed=950 + L, bh=[(0, 0), (0, 7), (0, H - 1)],
-               tag=f"split blocks L={L} H={H} D={D}")
+# groups (and four, causal D = 64 from L = 2049 on), dK/dV at D = 64 over two.
+@pytest.mark.parametrize("L,H,D,mode,groups", [
+    (700, 32, 64, "causal", (2, 2)), (700, 32, 64, "full", (2, 2)), (700, 32, 64, "docs", (2, 2)),
+    (1153, 40, 64, "causal", (2, 1)), (1153, 40, 64, "full", (2, 1)),
+    (2177, 20, 64, "causal", (4, 2)), (2177, 20, 64, "docs", (4, 2)),
+    (2177, 20, 64, "full", (2, 1)),
+    (900, 24, 128, "causal", (2, 1)), (900, 24, 128, "full", (2, 1)),
+    (2177, 20, 128, "causal", (2, 1)), (2177, 20, 128, "docs", (2, 1))])
+def test_grids_of_split_blocks(cuda, L, H, D, mode, groups):
+    assert routes.backward(1, L, H, D, mode != "full", mode == "docs") == groups
+    cu = dd.chunk_doclens([L // 3, 1, 20, L - L // 3 - 21], L) if mode == "docs" else None
+    check_case(1, L, H, D, causal=mode != "full", cu=cu, seed=950 + L,
+               bh=[(0, 0), (0, 7), (0, H - 1)], tag=f"split blocks L={L} H={H} D={D} {mode}")
 
 
 # Short rows take the persistent forms of the forward, dK/dV and (D = 64) dQ
@@ -102,14 +110,16 @@ def test_persistent_kernels_document_masked(cuda, D):
 # slice 256 further on, its inputs staged tile by tile during the previous
 # slice.  200 x 3 slices give two or three slices per workgroup; the sampled
 # slices 0, 256, 300, 512 and 599 are first, second and third slices of
-# their workgroups.  L = 200 leaves a ragged last query tile.
+# their workgroups.  L = 200 leaves a ragged last query tile, 129 and 255 are
+# the edges of the rows that this form takes.
 SHORT_PERSIST_BH = [(0, 0), (85, 1), (100, 0), (170, 2), (199, 2)]
 
 
-@pytest.mark.parametrize("L", [200, 256])
+@pytest.mark.parametrize("L", [129, 200, 255, 256])
 @pytest.mark.parametrize("mode", ["causal", "full", "docs"])
 def test_short_rows_persistent_several_slices(cuda, L, mode):
     B, H = 200, 3
+    assert routes.backward(B, L, H, 64, mode != "full", mode == "docs") == "short"
     cu = None
     if mode == "docs":
         lens = synth.lognormal_doc_lengths(L, total_tokens=B * L, median=L / 3, sigma=0.8)
@@ -130,15 +140,20 @@ def test_persistent_one_tile_items(cuda, B, L, H, doc):
                tag=f"persistent one-tile items B={B} L={L} doc={doc}")
 
 
-@pytest.mark.parametrize("B,L,D,causal", [(2, 700, 64, True), (2, 700, 128, False),
-                                         (1, 2100, 64, True), (1, 2100, 128, True)])
-def test_large_scores_forward(cuda, B, L, D, causal):
+@pytest.mark.parametrize("B,L,D,causal,groups", [
+    (2, 700, 64, True, 2), (2, 700, 128, False, 2), (1, 2100, 64, True, 4),
+    (1, 2100, 128, True, 2), (500, 700, 64, True, 1), (250, 700, 128, False, 1),
+    (50, 2100, 64, True, 1), (25, 2100, 128, True, 1)])
+def test_large_scores_forward(cuda, B, L, D, causal, groups):
     # Q and K times 8 (exact in bf16): the scaled scores in log2 units reach
     # several hundred, far outside exp2's fp32 range, so each tile's running
     # maximum must be the true maximum of its rows (a smaller one overflows
-    # the probabilities, a larger one underflows their sum).  L = 700 takes
-    # the persistent forward, L = 2100 one block per workgroup.
+    # the probabilities, a larger one underflows their sum).  Small grids share
+    # a block's keys over two or four groups of waves, whose maxima differ; the
+    # large grids take the persistent forward (L = 700) and one block per
+    # workgroup (L = 2100).
     H = 2
+    assert routes.forward(B, L, H, D, causal) == groups
     inputs = synth.attention_inputs(B, L, H, D, seed=21 + D, with_grad=False)
     for n in ("q", "k"):
         inputs[n] = synth.bf16_bits_from_f32(synth.f32_from_bf16_bits(inputs[n]) * 8.0)
@@ -146,7 +161,7 @@ def test_large_scores_forward(cuda, B, L, D, causal):
     out = gpu_run(inputs, causal, None, "cuda:0", backward=False)
     for n, t in out.items():
         assert bool(np.isfinite(t.float().cpu().numpy()).all()), f"{n} has non-finite values"
-    bh = [(b, h) for b in range(B) for h in range(H)]
+    bh = sorted({(0, 0), (B // 2, 1), (B - 1, 0), (B - 1, 1)})
     res = compare(inputs, out, causal, None, bh, backward=False, tag="large scores")
     assert_ok(res, backward=False)
 
@@ -213,17 +228,21 @@ def test_longest_bucket_sampled(cuda):
 
 
 # D = 64 rows of at most 256 tokens (without RoPE) take the one-kernel
-# backward, with a row capacity of 64, 128 or 256 tokens; each capacity is
-# covered at and around its edges, with the causal mask, without it, and
-# with documents.
-@pytest.mark.parametrize("L", [1, 31, 64, 65, 100, 128, 129, 255, 256])
+# backward, with a row capacity of 64, 128 or 256 tokens, the last one from 65
+# slices on (fewer take the joint launch); each capacity is covered at and
+# around its edges, with the causal mask, without it, and with documents.
+@pytest.mark.parametrize("B,L,route", [(3, L, "short") for L in (1, 31, 64, 65, 100, 128)]
+                         + [(3, L, "joint") for L in (129, 255, 256)]
+                         + [(45, L, "short") for L in (129, 255, 256)])
 @pytest.mark.parametrize("mode", ["causal", "full", "docs"])
-def test_short_rows_one_kernel_backward(cuda, L, mode):
-    B, H = 3, 2
+def test_short_rows_one_kernel_backward(cuda, B, L, route, mode):
+    H = 2
+    assert routes.backward(B, L, H, 64, mode != "full", mode == "docs") == route
     cu = None
     if mode == "docs":
         lens = synth.lognormal_doc_lengths(L, total_tokens=B * L, median=max(L / 3, 1.0),
                                            sigma=0.8)
         cu = dd.chunk_doclens(lens, B * L)
-    check_case(B, L, H, 64, causal=mode != "full", cu=cu, seed=300 + L,
-               tag=f"one-kernel backward L={L} {mode}")
+    bh = None if B == 3 else [(0, 0), (22, 1), (44, 1)]
+    check_case(B, L, H, 64, causal=mode != "full", cu=cu, seed=300 + L, bh=bh,
+               tag=f"{route} backward B={B} L={L} {mode}")

@@ -11,6 +11,7 @@ import numpy as np
 import pytest
 import torch
 
+import routes
 import synth
 import paper_2405_13226_amd as dd
 from paper_2405_13226_amd import _lib
@@ -59,7 +60,11 @@ def test_noalloc_backward_matches_workspace_backward(cuda):
     run_pair(4, 1000, 4, 128, cu, 1, cuda)      # first call
     run_pair(2, 300, 3, 64, None, 2, cuda)      # smaller, after it
     run_pair(3, 77, 2, 128, None, 3, cuda)      # smaller again, ragged
-    run_pair(2, 200, 2, 64, None, 4, cuda)      # one-kernel short-row path
+    run_pair(2, 200, 2, 64, None, 4, cuda)      # joint launch of a small grid
+    assert routes.backward(60, 200, 2, 64) == "short"
+    run_pair(60, 200, 2, 64, None, 7, cuda)     # one-kernel short-row path
+    assert routes.backward(48, 700, 3, 64) == (1, 1)
+    run_pair(48, 700, 3, 64, None, 8, cuda)     # dQ, then dK/dV
 
 
 def test_noalloc_backward_largest_scratch_shape(cuda):
