@@ -68,9 +68,6 @@ BF16_PEAK_TFLOPS = 2500.0   # MI355X dense bf16 matrix-core peak
 HBM_PEAK_GBS = 8000.0       # MI355X HBM3E
 METRIC = "attention fwd+bwd TFLOP/s and tokens/s per bucket at 65,536 tokens/step"
 BUCKETS = [256, 512, 1024, 2048, 4096, 8192]
-# D = 64 rows of at most this many tokens (without RoPE) run the one-kernel
-# backward.
-SHORT_MAX_ROW = 256
 
 
 def log(msg):
@@ -283,14 +280,26 @@ def workload(name, seed, buckets=None):
 # allowed (query, key) pair, per head dim, of each: the forward forms S and
 # O (4); dK/dV forms S, dP, dV and dK (8); dQ forms dQ (2: its S and dP are
 # recomputation); the one-kernel backward of D = 64 rows of at most 256
-# tokens without RoPE forms S, dP, dV, dK and dQ once (10).
-PER_PAIR = {"forward": 4, "backward_dkdv": 8, "backward_dq": 2, "backward_short": 10}
+# tokens without RoPE forms S, dP, dV, dK and dQ once (10), and so does, for
+# this count, the joint launch of dK/dV and dQ that small grids take (the
+# library books it, with its row terms, under the dK/dV id).
+PER_PAIR = {"forward": 4, "backward_dkdv": 8, "backward_dq": 2, "backward_short": 10,
+            "backward_joint": 10}
+
+# Kernels (names without template arguments) -> launch names of the counter
+# summaries; the row terms of the joint launch are a dispatch of their own.
+KERNEL_FAMILY = {"fwd_kernel": "forward", "dq_kernel": "backward_dq",
+                 "dkdv1_kernel": "backward_dkdv", "dkdv_kernel": "backward_dkdv",
+                 "bwd_short_kernel": "backward_short",
+                 "bwd_short_persist_kernel": "backward_short", "rope_kernel": "rope",
+                 "bwd_rows_kernel": "backward_rows", "bwd_pair_kernel": "backward_joint"}
 
 
 def split_by_group(launches, names, n_groups):
-    """[(kernel name, ms)] in launch order -> per group {kernel: [ms, ...]}.
+    """[(kernel id, value)] in launch order -> per group {name: [value, ...]}.
     Every group launches exactly one forward per step, preceded by its RoPE
-    launches (if any) and followed by its backward kernels."""
+    launches (if any) and followed by its backward kernels; dK/dV without a dQ
+    launch is the joint launch of both."""
     out = [dict() for _ in range(n_groups)]
     gi = -1
     for kid, ms in launches:
@@ -303,6 +312,9 @@ def split_by_group(launches, names, n_groups):
         else:
             target = gi
         out[target].setdefault(name, []).append(ms)
+    for g in out:
+        if "backward_dkdv" in g and "backward_dq" not in g:
+            g["backward_joint"] = g.pop("backward_dkdv")
     return out
 
 
@@ -845,9 +857,7 @@ def traffic_summary(args):
 
     import numpy as np
 
-    fam = {"fwd_kernel": "forward", "dq_kernel": "backward_dq", "dkdv1_kernel": "backward_dkdv",
-           "dkdv_kernel": "backward_dkdv", "bwd_short_kernel": "backward_short",
-           "bwd_short_persist_kernel": "backward_short", "rope_kernel": "rope"}
+    fam = KERNEL_FAMILY
 
     def read(d, counter):
         f = glob.glob(os.path.join(d, "**", "*counter_collection.csv"), recursive=True)
@@ -878,6 +888,8 @@ def traffic_summary(args):
         for n, v in rows:
             m = re.search(r"dd::(\w+)", n)
             if m and m.group(1) in fam:
+                if lib_rows and lib_rows[-1][0] == "backward_rows":
+                    v += lib_rows.pop()[1] / scale  # part of the joint launch that follows
                 lib_rows.append((fam[m.group(1)], v * scale))
         out[counter] = (scale, lib_rows)
     groups, desc = workload(args.workload, args.seed,
@@ -907,9 +919,7 @@ def traffic_summary(args):
         while start > 0 and names[start - 1] == "rope":
             start -= 1
         tail = lib_rows[start:]
-        kid = {"forward": 0, "rope": 4, "backward_dq": 3, "backward_dkdv": 2, "backward_short": 1}
-        nm = {v: k for k, v in kid.items()}
-        by = split_by_group([(kid[n], v) for n, v in tail], nm, len(groups))
+        by = split_by_group(tail, {n: n for n, _ in tail}, len(groups))
         for g, kl in zip(groups, by):
             for kname, vals in kl.items():
                 out.setdefault("_bytes", {}).setdefault((kname, g["name"]), {})[key] = \
@@ -934,10 +944,7 @@ def sq_summary(args):
     import glob
     import re
 
-    fam = {"fwd_kernel": "forward", "dq_kernel": "backward_dq", "dkdv1_kernel": "backward_dkdv",
-           "dkdv_kernel": "backward_dkdv", "bwd_short_kernel": "backward_short",
-           "bwd_short_persist_kernel": "backward_short", "rope_kernel": "rope"}
-    kid = {"forward": 0, "rope": 4, "backward_dq": 3, "backward_dkdv": 2, "backward_short": 1}
+    fam = KERNEL_FAMILY
 
     def read(d):
         f = glob.glob(os.path.join(d, "**", "*counter_collection.csv"), recursive=True)
@@ -975,13 +982,13 @@ def sq_summary(args):
         if a["kernel"] != b["kernel"]:
             raise SystemExit("the two passes hold different launch sequences")
         merged.append({**b, **a})
-    nm = {v: k for k, v in kid.items()}
-    by = split_by_group([(kid[m["fam"]], m) for m in merged], nm, len(groups))
+    by = split_by_group([(m["fam"], m) for m in merged], {m["fam"]: m["fam"] for m in merged},
+                        len(groups))
     lines = ["| L | kernel | ms | SCLK GHz | MFMA busy % | MFMA+VALU co-issue % | waves waiting % "
              "| waiting to issue % | waiting on LDS issue % | VALU / MFMA instr | LDS / MFMA instr |",
              "|---|---|---|---|---|---|---|---|---|---|---|"]
     for g, kl in zip(groups, by):
-        for fname in ("rope", "forward", "backward_short", "backward_dq", "backward_dkdv"):
+        for fname in dict.fromkeys(("rope", "forward", *fam.values())):
             for m in kl.get(fname, []):
                 gui = m["GRBM_GUI_ACTIVE"] / 8.0
                 simd = gui * 1024.0

@@ -326,10 +326,26 @@ def test_kernel_ids_match_the_library(lib):
     assert lib.dd_prof_kernel_name(-1) is None
 
 
-def test_bench_counts_the_one_kernel_backward_where_the_library_runs_it():
-    # bench.py's FLOP accounting assumes the one-kernel backward runs for
-    # D = 64 rows up to the library's limit (kShortMaxRow).
+def test_bench_counts_every_backward_launch_once():
+    # Whichever launches the library books for a backward, they add up to its
+    # 10 D FLOPs per pair: dQ and dK/dV, the one-kernel form, or the joint
+    # launch of small grids, booked as dK/dV alone.
     import bench
-    text = open(os.path.join(ROOT, "paper_2405_13226_amd", "csrc", "dd_bwd.hpp")).read()
-    m = re.search(r"constexpr int kShortMaxRow = (\d+);", text)
-    assert m and int(m.group(1)) == bench.SHORT_MAX_ROW
+    names = {kid: n for n, kid in _lib.KERNELS.items()}
+    fwd, dkdv, dq, short = (_lib.KERNELS[n] for n in ("forward", "backward_dkdv", "backward_dq",
+                                                      "backward_short"))
+    g = dict(D=64, pairs=100)
+    for launches in ([(dq, 1.0), (dkdv, 1.0)], [(short, 1.0)], [(dkdv, 1.0)]):
+        (by,) = bench.split_by_group([(fwd, 1.0)] + launches, names, 1)
+        flops = sum(bench.kernel_alg(n, g)[0] for n in by if n != "forward")
+        assert flops == 10 * 64 * 100, by
+
+
+def test_counter_summaries_know_every_attention_kernel():
+    import bench
+    csrc = os.path.join(ROOT, "paper_2405_13226_amd", "csrc")
+    kernels = set()
+    for src in ("dd_fwd.hip", "dd_bwd.hip", "dd_dkdv.hip", "dd_bwd_short.hip", "dd_rope.hip"):
+        text = open(os.path.join(csrc, src)).read()
+        kernels |= set(re.findall(r"__global__ void __launch_bounds__\([^{;]*?\)\s*\n(\w+)\(", text))
+    assert len(kernels) >= 8 and kernels <= set(bench.KERNEL_FAMILY), kernels

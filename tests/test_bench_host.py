@@ -96,3 +96,24 @@ def test_cpu_baseline_counts_every_sampled_slice():
     cu = [0, 3, 10, 16]  # rows of 8: [0,3) [3,8) | [8,10) [10,16)
     assert list(bench.row_pairs(2, 8, cu)) == [6 + 15, 3 + 21]
     assert bench.sample_flops([(1, 0), (1, 5), (0, 2)], 2, 8, 64, cu) == 14 * 64 * (24 + 24 + 21)
+
+
+def test_traffic_summary_adds_the_joint_backwards_row_terms(tmp_path):
+    # A small grid's backward: the row terms' dispatch, then the joint one.
+    def rows(per_kib):
+        r = [("void at::native::copy_kernel", 2 ** 20)] * 3
+        for _ in range(2):
+            r += [("void dd::fwd_kernel<64, false, false, 2>(...)", 100.0 * per_kib),
+                  ("void dd::bwd_rows_kernel<64>(...)", 10.0 * per_kib),
+                  ("void dd::bwd_pair_kernel<64>(...)", 300.0 * per_kib)]
+        return r
+    _write_counters(tmp_path / "f", "FETCH_SIZE", rows(1.0))
+    _write_counters(tmp_path / "w", "WRITE_SIZE", rows(0.5))
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    out = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--workload",
+                          "dd_sweep_d64", "--buckets", "256", "--traffic-summary",
+                          str(tmp_path / "f"), str(tmp_path / "w")],
+                         capture_output=True, text=True, check=True).stdout
+    assert f"fetch_bytes_per_launch.backward_joint.L=256 = {310 * 1024}" in out
+    assert f"write_bytes_per_launch.backward_joint.L=256 = {155 * 1024}" in out
+    assert "backward_rows" not in out
