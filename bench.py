@@ -702,10 +702,10 @@ def run_gemm(args, dev):
     from paper_2405_13226_amd.layer import OPENLM_1B
 
     T, d, hid = TOKENS, OPENLM_1B["d"], OPENLM_1B["hidden"]
-    # (name, M, N, K, trans_a, trans_b): y = x (W^T)^T (weights stored [N][K]),
+    # (name, M, N, K, trans_a, trans_b), the forms of the block: y = x W,
     # dx = dy W^T, dW = x^T dy
-    shapes = [("qkv fwd", T, 3 * d, d, 0, 1), ("out fwd", T, d, d, 0, 1),
-              ("w1 fwd", T, hid, d, 0, 1), ("w2 fwd", T, d, hid, 0, 1),
+    shapes = [("qkv fwd", T, 3 * d, d, 0, 0), ("out fwd", T, d, d, 0, 0),
+              ("w1 fwd", T, hid, d, 0, 0), ("w2 fwd", T, d, hid, 0, 0),
               ("qkv dx", T, d, 3 * d, 0, 1), ("w1 dx", T, d, hid, 0, 1),
               ("w2 dx", T, hid, d, 0, 1), ("qkv dW", d, 3 * d, T, 1, 0),
               ("w1 dW", d, hid, T, 1, 0), ("w2 dW", hid, d, T, 1, 0)]
