@@ -256,9 +256,11 @@ __device__ __forceinline__ int wave_max(int v)
 // and the last row's: two scalar reads instead of four reductions of six
 // dependent lane exchanges.  Nothing of a wave without rows (row0 >= L) is
 // used.  Together with starting an item's first tile loads before its row
-// loads, the backward of 128 x 512 rows at D = 128 went from 1,040 to 1,017
-// us, of 256 x 256 at D = 64 from 311 to 305; the forward's split form was 2%
-// slower with it and keeps the reductions.
+// loads it takes a tenth of the LDS operations off short rows (128 x 512 at D
+// = 128: 1.46 -> 1.34 per product in dQ, 2.17 -> 2.00 in dK/dV), but little
+// time: dQ 473 -> 480 us, dK/dV 568 -> 555; a whole call 1,249 -> 1,252, of
+// 256 x 256 rows at D = 64 443 -> 441.  The forward's split form was 2% slower
+// with it and keeps the reductions.
 __device__ __forceinline__ void wave_bounds(int lo, int hi, int row0, int L, int &lo_w, int &hi_w,
                                             int &lo_all, int &hi_all)
 {

@@ -30,13 +30,15 @@
 // and waits are explicit: the compiler would otherwise wait for every load
 // before each transposing LDS read.
 //
-// What bounds it: power.  At 8192^3 the matrix pipes are busy 87% of the
-// time (0.50 with one barrier per step and all waves in phase) at a shader
-// clock of 1.5-1.6 GHz; the 32x32x16 product keeps them 89% busy at 1.35 GHz
-// and is 7% slower, so the 16x16x32 product is used.  Measured (TFLOP/s,
-// before -> now): 8192^3 A B^T 1,134 -> 1,480, A B 1,068 -> 1,373, A^T B 997
-// -> 1,420; 65,536 x 5632 x 2048 A B^T 1,151 -> 1,420; 2048 x 5632 x 65,536
-// A^T B 863 -> 1,173.
+// What bounds it: power.  At 8192^3 the matrix pipes are busy 76-83% of the
+// time (50% with one barrier per step and all waves in phase) at a shader
+// clock of 1.4-1.6 GHz of 2.4; the 32x32x16 product kept them 89% busy at 1.35
+// GHz and was 7% slower, so the 16x16x32 product is used.  At K = 2048 they
+// are busy 69-75%: tile starts and ends.  Measured (TFLOP/s, one barrier per
+// step -> now): 8192^3 A B^T 1,134 -> 1,480-1,565, A B 1,068 -> 1,373-1,555
+// (within 1% of A B^T where both were timed in one process), A^T B 997 ->
+// 1,420; 65,536 x 5632 x 2048 A B^T 1,151 -> 1,410; 2048 x 5632 x 65,536 A^T B
+// 863 -> 1,173-1,220.
 //
 // Every 64 x 64 sub-tile sits in LDS as the matrix stores it, 128-byte rows
 // of swizzled 16-byte chunks.  An operand stored with its reduction axis
@@ -516,12 +518,14 @@ gemm_kernel(GemmOperands op, GemmSizes sz)
 // are in flight: three of four for the small tile (128 KiB; two or four more
 // measured the same or slower), two of three for the tall one (144 KiB).
 //
-// What bounds the loop: the LDS, 128 bytes per clock.  A step of the small
-// tile reads 96 KiB and receives 32 (1024 clocks; 0.41 us measured), of the
-// tall one 128 and 48 (1408 clocks; 0.60), of the large one 192 and 64
-// (2048 clocks, its products' time).  Letting each group take half of the
-// k for the whole small tile reads 64 KiB a step and measured 6% faster at
-// K = 5632, 5% slower at K = 1024 (the sums have to be added at the end).
+// What bounds the loop: no throughput, but the turn of the two groups.  A step
+// of the small tile takes 0.41 us (about 900 clocks), of which its products
+// fill 512 and its 96 KiB of LDS reads about as many (220-256 bytes per clock
+// measured); of the tall one 0.60 us (1024 clocks of products, 128 KiB).
+// Waves wait at barriers and for loads 31-42% of their cycles and to issue
+// 29-39%, of that on LDS 6-12%.  Letting each group take half of the k for the
+// whole small tile reads 64 KiB a step and measured 6% faster at K = 5632, 5%
+// slower at K = 1024 (the sums have to be added at the end).
 // 2048 x 1024 x 1024: 21.1 us on 32 large tiles, 11.4-12.6 on small ones.
 struct SmallTile {
     static constexpr int BM = 128, BN = 128, BK = 64, NST = 4;
