@@ -30,6 +30,7 @@
 #include "dd_launch.hpp"
 #include "dd_tile.hpp"
 
+#include <climits>
 
 namespace dd {
 
@@ -252,10 +253,18 @@ bwd_short_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
     int qlo_k = 1, qhi_k = 0;
     if (k_ok)
         key_queries(b, L, my_k, causal, cu, n_docs, qlo_k, qhi_k);
-    int lo_w, hi_w, lo_all, hi_all;
-    wave_bounds(qlo_k, qhi_k, wave * 32, L, lo_w, hi_w, lo_all, hi_all);
-    if (wave * 32 >= L)
-        hi_w = -1;  // no keys: every tile is skipped
+    // The wave's query range by reductions with 64 rows, by two lanes' values
+    // with 128: us of 16 slices 6.8 / 7.2 at L = 64, 10.7 / 10.6 at L = 128.
+    int lo_w, hi_w;
+    if constexpr (ROWS == 64) {
+        lo_w = wave_min(k_ok ? qlo_k : INT_MAX);
+        hi_w = wave_max(k_ok ? qhi_k : -1);
+    } else {
+        int lo_all, hi_all;
+        wave_bounds(qlo_k, qhi_k, wave * 32, L, lo_w, hi_w, lo_all, hi_all);
+        if (wave * 32 >= L)
+            hi_w = -1;  // no keys: every tile is skipped
+    }
 
     ShortOffsets o;
     o.init(lane);
