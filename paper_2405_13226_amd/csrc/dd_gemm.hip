@@ -32,7 +32,7 @@
 //
 // What bounds it: power.  At 8192^3 the matrix pipes are busy 76-83% of the
 // time (50% with one barrier per step and all waves in phase) at a shader
-// clock of 1.4-1.6 GHz of 2.4; the 32x32x16 product kept them 89% busy at 1.35
+// clock of 1.4-1.7 GHz of 2.4; the 32x32x16 product kept them 89% busy at 1.35
 // GHz and was 7% slower, so the 16x16x32 product is used.  At K = 2048 they
 // are busy 69-75%: tile starts and ends.  Measured (TFLOP/s, one barrier per
 // step -> now): 8192^3 A B^T 1,134 -> 1,480-1,565, A B 1,068 -> 1,373-1,555
@@ -522,7 +522,7 @@ gemm_kernel(GemmOperands op, GemmSizes sz)
 // of the small tile takes 0.41 us (about 900 clocks), of which its products
 // fill 512 and its 96 KiB of LDS reads about as many (220-256 bytes per clock
 // measured); of the tall one 0.60 us (1024 clocks of products, 128 KiB).
-// Waves wait at barriers and for loads 31-42% of their cycles and to issue
+// Waves wait at barriers and for loads 31-43% of their cycles and to issue
 // 29-39%, of that on LDS 6-12%.  Letting each group take half of the k for the
 // whole small tile reads 64 KiB a step and measured 6% faster at K = 5632, 5%
 // slower at K = 1024 (the sums have to be added at the end).
